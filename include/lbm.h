@@ -159,7 +159,9 @@ lbm_status lbm_init_fields(lbm_handle *h, const double *phi, const double *psi,
 /* Advance nsteps >= 0 time steps: each is one launch of the fused
  * stream-collide kernel (pull streaming with half-way bounce-back, the
  * gradient stencils, forces, closures (32a)-(32b), and the three MRT
- * collisions of Eqs. (21), (25), (29) in moment space).  Asynchronous.
+ * collisions of Eqs. (21), (25), (29) in moment space).  On a grid too small
+ * to fill the device a launch takes up to three steps (the same results);
+ * it uses the read-back scratch of the workspace meanwhile.  Asynchronous.
  * Errors: LBM_EINVAL (nsteps < 0), LBM_ESTATE, LBM_EDEVICE. */
 lbm_status lbm_step(lbm_handle *h, int64_t nsteps);
 
@@ -251,6 +253,7 @@ const char *lbm_last_error(const lbm_handle *h);
  * about one wavefront's walk down its tile); for float16 storage with two
  * columns per lane, one tile per wavefront slot of the device when such
  * tiles are at most 24 rows high; otherwise a height tuned for large grids.
+ * A height other than 0 also makes every step a launch of its own.
  * Results do not depend on the tiling.
  * Errors: LBM_EINVAL (< 0 or > 4096). */
 lbm_status lbm_set_tile_rows(lbm_handle *h, int32_t rows);
@@ -261,7 +264,7 @@ lbm_status lbm_set_tile_rows(lbm_handle *h, int32_t rows);
  * int32_t, written only on success.  Errors: LBM_EINVAL (NULL). */
 lbm_status lbm_get_tile_plan(const lbm_handle *h, int32_t *plan);
 
-/* The step kernel variant lbm_step launches for this handle, named as a
+/* The single-step kernel variant of lbm_step for this handle, named as a
  * profiler prints its template arguments, e.g.
  * "lbm_step_kernel<F32, 2, false, true, true>": storage (F64, F32, F16; F64C
  * and F32C store with the default cache policy), columns per lane, r != 1,

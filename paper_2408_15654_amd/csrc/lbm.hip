@@ -968,6 +968,14 @@ struct Pull2 {
   }
 };
 
+// Which product of the phase-field and surfactant sources is fused
+// (collide_fg): the float16 kernels take the first one written, the time
+// difference; the others what the compiler used to choose for them.
+template <class P, bool NS>
+constexpr bool kFluxF = NS && !P::SCALED;
+template <class P, bool NS, bool GENR>
+constexpr bool kFluxG = NS && !P::SCALED && !(GENR && sizeof(typename P::R) == 8);
+
 // The fused step: pull-stream + boundaries, phi/psi/sigma, stencils, forces,
 // closures, three MRT collisions, store.  Each lane holds K adjacent
 // columns.  The two columns on each side of the interior are halo: they
@@ -1285,7 +1293,7 @@ __device__ __forceinline__ void step_tile(const StepArgs<P> &a, const int strip,
 
       Front<R> s;
       if constexpr (NS)
-        site_front<R, HAS_S>(p, s, phc[k], psc[k], sgc[k], gfx, gfy, lphi, gsx, gsy, h[k], php,
+        site_front<R, HAS_S, !P::SCALED>(p, s, phc[k], psc[k], sgc[k], gfx, gfy, lphi, gsx, gsy, h[k], php,
                              psp, uxp[k], uyp[k], Sxp[k], Syp[k]);
       else
         site_front_prescribed<R>(p, s, phc[k], psc[k], gfx, gfy, uxp[k], uyp[k], php, psp);
@@ -1296,9 +1304,9 @@ __device__ __forceinline__ void step_tile(const StepArgs<P> &a, const int strip,
         s.gpx = s.gpy = R(0);
       }
       if constexpr (NS)
-        collide_site<R, GENR>(p, s, dc[k], qc[k], h[k]);
+        collide_site<R, GENR, kFluxF<P, NS>, kFluxG<P, NS, GENR>>(p, s, dc[k], qc[k], h[k]);
       else
-        collide_fg<R, GENR>(p, s, dc[k], qc[k]);
+        collide_fg<R, GENR, kFluxF<P, NS>, kFluxG<P, NS, GENR>>(p, s, dc[k], qc[k]);
       if constexpr (P::HDEV && NS) {  // h as deviations from this site's new rest parts
 #pragma clang fp contract(off)
         hn.pr[k] = s.P;
@@ -1522,6 +1530,412 @@ lbm_step_kernel(const StepArgs<P> a) {
   const int y0 = full ? b.y0 + chunk * a.rows : b.ys + (chunk - b.nlong) * a.tail_h;
   const int y1 = full ? min(y0 + a.rows, b.ys) : min(y0 + a.tail_h, b.y1);
   step_tile<P, K, GENR, HAS_S, NS>(a, tile - chunk * a.nstrips, y0, y1);
+}
+
+
+// ------------------------------------------------- several steps per launch
+
+// Block step: one workgroup advances a 16 x 16 block of sites `steps` time
+// steps in LDS, one thread per site, and stores the sites whose every
+// dependence lay inside the block.  A step reaches two sites in every
+// direction (a site pulls from its neighbours, and its stencils need the
+// phi, psi, sigma that its neighbours rebuild from theirs), so `steps` steps
+// leave 16 - 2 (2 steps - 1) sites a side, the blocks of neighbouring
+// workgroups overlap, and no workgroup waits for another.
+//
+// What bounds it: latency.  On a grid too small to fill the device a step of
+// lbm_step_kernel is one wavefront's walk (6.5 us for float32 storage: three
+// row rebuilds and a collision of two columns in one wavefront, 1700 vector
+// instructions, after a round trip to memory and between two launches).
+// Here a launch costs 3.0 us once (launch, loads, stores) and each step
+// 1.5 us (one rebuild and one collision per wavefront, 700 instructions at
+// one wavefront per SIMD, and two barriers); float64 2.3 us, float16 2.9 us.
+// Measured per step on MI355X, lbm_step_kernel -> this (steps per launch):
+// 64^2 float32 6.5 -> 2.7 us (3), float64 7.2 -> 3.1 us (3), float16
+// 7.9 -> 4.0 us (3); 128^2 float32 6.6 -> 3.4 us (2); 256x128 float32
+// 6.8 -> 4.0 us (2).  Larger blocks (32 x 16, 32 x 32 threads) waste fewer
+// sites but put 2 and 4 wavefronts on a SIMD: 64^2 float32 3.3 us, 256x128
+// 4.3 and 8.3 us.  Asking for 3 or 4 wavefronts per SIMD spills (256x128:
+// 4.9 and 7.2 us).
+//
+// Each XCD takes a contiguous run of blocks: with blocks dealt round-robin
+// the lines that neighbouring blocks share came through two L2s (256x128
+// float32 6.3 us per step).
+//
+// The arithmetic of a site is that of step_tile, bit for bit, in every
+// precision: the float16 kernels by their compilation pass, the others by
+// the expressions spelled out with fused() (lbm_device.h).
+constexpr int kBlockSide = 16;
+constexpr int kBlockMaxSteps = 3;
+
+template <class P>
+struct BlockArgs {
+  StepArgs<P> s;
+  typename P::A *aux_out;  // new previous velocity (s.aux is read by several blocks)
+  int steps;               // time steps of this launch
+  int ntx, ntiles;         // blocks per row of blocks, in all
+};
+
+// Columns and rows of the block on each side that the last of `steps` steps
+// cannot form.  Float16 storage with even nx rounds h in pairs of columns,
+// both of which must be formed, and starts its blocks on even columns.
+template <class P>
+__host__ __device__ constexpr int block_halo_x(int steps) {
+  return P::SCALED ? 2 * steps : 2 * steps - 1;
+}
+__host__ __device__ constexpr int block_halo_y(int steps) { return 2 * steps - 1; }
+
+// Value of the other lane of an even/odd pair of lanes (quad permutation
+// 1, 0, 3, 2).
+__device__ __forceinline__ float pair_lane(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xf, 0xf, true));
+}
+
+template <class T>
+struct Two {
+  T a, b;
+};
+
+template <class P, bool GENR, bool HAS_S, bool NS>
+__global__ void __launch_bounds__(kBlockSide * kBlockSide)
+lbm_block_kernel(const BlockArgs<P> ba) {
+  using R = typename P::R;
+  using S = typename P::S;
+  using A = typename P::A;
+  constexpr int B = kBlockSide, N = B * B;
+  static_assert(B > 2 * block_halo_x<P>(kBlockMaxSteps), "no site left after the last step");
+  constexpr unsigned ES = sizeof(S), EA = sizeof(A);
+  constexpr int NH = NS ? 8 : 1, NR = P::HDEV && NS ? 3 : 1;
+  // one step's post-collision state of the block, in storage form, and the
+  // scalars of the level being formed
+  __shared__ Two<S> l_fg[8][N];       // f_i, g_i, i = 1..8
+  __shared__ S l_h[NH][N];            // h_1..h_8
+  __shared__ Two<A> l_rest[2][N];     // phi, psi of two levels
+  __shared__ A l_sig[N];
+  __shared__ A l_hr[NR][N];           // float16 storage: P, rho ux, rho uy
+
+  const StepArgs<P> &a = ba.s;
+  const Phys<R> &p = a.p;
+  const Scales<P> &sc = a.sc;
+  const int nx = a.nx, ny = a.ny, walls = a.walls, steps = ba.steps;
+  const int hx = block_halo_x<P>(steps), hy = block_halo_y(steps);
+  // workgroup b runs on XCD b % 8: each XCD takes a contiguous run of blocks,
+  // which read the columns and rows they share through one L2
+  const int per = int(gridDim.x) / kXcds;
+  const int tile = int(blockIdx.x % kXcds) * per + int(blockIdx.x / kXcds);
+  if (tile >= ba.ntiles) return;
+  const int ty = tile / ba.ntx, tx = tile - ty * ba.ntx;
+  const int lx = int(threadIdx.x) % B, ly = int(threadIdx.x) / B;
+  const int gx = tx * (B - 2 * hx) - hx + lx, gy = ty * (B - 2 * hy) - hy + ly;
+  const bool owned = lx >= hx && lx < B - hx && ly >= hy && ly < B - hy && gx < nx && gy < ny;
+  int x = gx % nx, y = gy % ny;
+  if (x < 0) x += nx;
+  if (y < 0) y += ny;
+  if (walls) y = gy < 0 ? 0 : (gy >= ny ? ny - 1 : gy);  // rows past a wall are never used
+  const bool bot = walls && y == 0, top = walls && y == ny - 1;
+  const bool even = P::SCALED && nx % 2 == 0;  // h rounded in pairs of columns
+
+  // neighbours in the block; at a wall the stencils' row beyond it is the
+  // wall row itself
+  const int k0 = ly * B + lx;
+  const int dl = lx > 0 ? -1 : 0, dr = lx < B - 1 ? 1 : 0;
+  const int dm = ly > 0 && !bot ? -B : 0, dp = ly < B - 1 && !top ? B : 0;
+  auto nine = [&](auto get) {
+    Nine<R> v;
+    v.mL = R(get(k0 + dm + dl));
+    v.m = R(get(k0 + dm));
+    v.mR = R(get(k0 + dm + dr));
+    v.cL = R(get(k0 + dl));
+    v.c = R(get(k0));
+    v.cR = R(get(k0 + dr));
+    v.nL = R(get(k0 + dp + dl));
+    v.n = R(get(k0 + dp));
+    v.nR = R(get(k0 + dp + dr));
+    return v;
+  };
+  R d[9], q[9], h[8];
+  Nine<R> X, Y, HP, HX, HY;  // previous level: phi, psi; P, rho ux, rho uy
+  R uxp = R(0), uyp = R(0);
+  bool bad = false;
+  const unsigned ux_ = unsigned(x), uy_ = unsigned(y), unx = unsigned(nx);
+  const unsigned nxb = unx * 2 * ES, nxh = unx * ES, hb = 9u * nxb;
+  const unsigned rows_s = unsigned(kPlanes) * nxh;
+
+  auto decode = [&](const Two<S> &w, int i) {
+#pragma clang fp contract(off)
+    if constexpr (P::SCALED) {
+      d[i] = even ? scale_half(float(w.a), sc.fi) : R(w.a) * sc.fi;
+      q[i] = even ? scale_half(float(w.b), sc.gi) : R(w.b) * sc.gi;
+    } else {
+      d[i] = R(w.a);
+      q[i] = R(w.b);
+    }
+  };
+  auto decode_h = [&](S w, int k) {
+#pragma clang fp contract(off)
+    if constexpr (P::SCALED)
+      h[k] = even ? scale_half(float(w), sc.hi) : R(w) * sc.hi;
+    else
+      h[k] = R(w);
+  };
+
+  {  // first step: the state comes from memory
+    const unsigned nsites = unx * unsigned(ny);
+    const rsrc_t rsrc = make_rsrc(a.src, unsigned(kPlanes) * nsites * ES);
+    const rsrc_t rrest = make_rsrc(a.src_rest, unsigned(P::kRest) * nsites * EA);
+    const rsrc_t raux = make_rsrc(a.aux, unsigned(P::kAux) * nsites * EA);
+    const unsigned xm = x == 0 ? unx - 1 : ux_ - 1, xp = x == nx - 1 ? 0u : ux_ + 1;
+    const unsigned ym = y == 0 ? (walls ? 0u : unsigned(ny - 1)) : uy_ - 1;
+    const unsigned yp = y == ny - 1 ? (walls ? uy_ : 0u) : uy_ + 1;
+    const unsigned rc = uy_ * rows_s, rm = ym * rows_s, rp = yp * rows_s;
+    Two<S> w[9];
+    auto pair = [&](unsigned row, unsigned col, int i) {
+      PairIO<S>::load(rsrc, row + col * 2 * ES, 0, w[i].a, w[i].b);
+    };
+    pair(rc, ux_, 0);
+    pair(rc + nxb, xm, 1);
+    pair(rc + 3 * nxb, xp, 3);
+    pair(bot ? rc + 4 * nxb : rm + 2 * nxb, ux_, 2);
+    pair(bot ? rc + 7 * nxb : rm + 5 * nxb, bot ? ux_ : xm, 5);
+    pair(bot ? rc + 8 * nxb : rm + 6 * nxb, bot ? ux_ : xp, 6);
+    pair(top ? rc + 2 * nxb : rp + 4 * nxb, ux_, 4);
+    pair(top ? rc + 5 * nxb : rp + 7 * nxb, top ? ux_ : xp, 7);
+    pair(top ? rc + 6 * nxb : rp + 8 * nxb, top ? ux_ : xm, 8);
+    auto rest = [&](unsigned yy, unsigned xx, R &u, R &v) {
+      A s, t;
+      PairIO<A>::load(rrest, (yy * unx + xx) * (P::kRest * EA), 0, s, t);
+      u = R(s);
+      v = R(t);
+    };
+    rest(ym, xm, X.mL, Y.mL);
+    rest(ym, ux_, X.m, Y.m);
+    rest(ym, xp, X.mR, Y.mR);
+    rest(uy_, xm, X.cL, Y.cL);
+    rest(uy_, ux_, X.c, Y.c);
+    rest(uy_, xp, X.cR, Y.cR);
+    rest(yp, xm, X.nL, Y.nL);
+    rest(yp, ux_, X.n, Y.n);
+    rest(yp, xp, X.nR, Y.nR);
+    if constexpr (P::HDEV && NS) {
+      auto hrest = [&](unsigned yy, unsigned xx, R &u, R &v, R &t) {
+        TripleIO::load(rrest, (yy * unx + xx) * (P::kRest * EA) + 2 * EA, 0, u, v, t);
+      };
+      hrest(ym, xm, HP.mL, HX.mL, HY.mL);
+      hrest(ym, ux_, HP.m, HX.m, HY.m);
+      hrest(ym, xp, HP.mR, HX.mR, HY.mR);
+      hrest(uy_, xm, HP.cL, HX.cL, HY.cL);
+      hrest(uy_, ux_, HP.c, HX.c, HY.c);
+      hrest(uy_, xp, HP.cR, HX.cR, HY.cR);
+      hrest(yp, xm, HP.nL, HX.nL, HY.nL);
+      hrest(yp, ux_, HP.n, HX.n, HY.n);
+      hrest(yp, xp, HP.nR, HX.nR, HY.nR);
+    }
+    S wh[8];
+    if constexpr (NS) {
+      auto one = [&](unsigned row, unsigned col, int k) {
+        wh[k] = BufIO<S>::load(rsrc, row + hb + col * ES, 0);
+      };
+      one(rc, xm, 0);
+      one(rc + 2 * nxh, xp, 2);
+      one(bot ? rc + 3 * nxh : rm + nxh, ux_, 1);
+      one(bot ? rc + 6 * nxh : rm + 4 * nxh, bot ? ux_ : xm, 4);
+      one(bot ? rc + 7 * nxh : rm + 5 * nxh, bot ? ux_ : xp, 5);
+      one(top ? rc + nxh : rp + 3 * nxh, ux_, 3);
+      one(top ? rc + 4 * nxh : rp + 6 * nxh, top ? ux_ : xp, 6);
+      one(top ? rc + 5 * nxh : rp + 7 * nxh, top ? ux_ : xm, 7);
+    }
+    if constexpr (!P::HDEV || !NS) {
+      A s, t;
+      PairIO<A>::load(raux, (uy_ * unx + ux_) * (P::kAux * EA), 0, s, t);
+      uxp = R(s);
+      uyp = R(t);
+    }
+#pragma unroll
+    for (int i = 0; i < 9; ++i) decode(w[i], i);
+    if constexpr (NS) {
+#pragma unroll
+      for (int k = 0; k < 8; ++k) decode_h(wh[k], k);
+    }
+  }
+
+  for (int t = 0;; ++t) {
+    // rebuild phi, psi, sigma of the new level from the pulled deviations
+    R e[9];
+    source_offsets(X, bot, top, e);
+    const R ph = restream(d, e, X.c);
+    source_offsets(Y, bot, top, e);
+    const R ps = restream(q, e, Y.c);
+    const R sg = sigma_of(p, ps);
+    Two<A> rec;
+    rec.a = A(ph);
+    rec.b = A(ps);
+    l_rest[t & 1][k0] = rec;
+    l_sig[k0] = A(sg);
+    // the previous level's mass flux, Eq. (16)
+    R Sxp = R(0), Syp = R(0);
+    if constexpr (HAS_S && NS) {
+      R fx, fy;
+      grad9(X, fx, fy);
+      mass_flux(p, X.c, fx, fy, Sxp, Syp);
+    }
+    if constexpr (P::HDEV && NS) {  // rest parts of the arriving h
+#pragma clang fp contract(off)
+      R b[8];
+      h_arrival_basis(HP, HX, HY, bot, top, b);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) h[i] += b[i];
+      const R irho = recip(p.rhoB + p.drho * (X.c - p.phiB));
+      uxp = HX.c * irho;
+      uyp = HY.c * irho;
+    }
+    if constexpr (NS) wall_terms(bot, top, rho_of(p, X.c), p.uwb, p.uwt, h);
+    const R php = X.c, psp = Y.c;
+    __syncthreads();
+    const Nine<R> vphi = nine([&](int k) { return l_rest[t & 1][k].a; });
+    const Nine<R> vsig = nine([&](int k) { return l_sig[k]; });
+    R gfx, gfy, gsx, gsy;
+    grad9(vphi, gfx, gfy);
+    grad9(vsig, gsx, gsy);
+    const R lphi = lap9(vphi);
+    Front<R> s;
+    if constexpr (NS)
+      site_front<R, HAS_S, !P::SCALED>(p, s, ph, ps, sg, gfx, gfy, lphi, gsx, gsy, h, php, psp, uxp, uyp,
+                           Sxp, Syp);
+    else
+      site_front_prescribed<R>(p, s, ph, ps, gfx, gfy, uxp, uyp, php, psp);
+    if constexpr (GENR) {
+      const Nine<R> vpsi = nine([&](int k) { return l_rest[t & 1][k].b; });
+      grad9(vpsi, s.gpx, s.gpy);
+    } else {
+      s.gpx = s.gpy = R(0);
+    }
+    if constexpr (NS)
+      collide_site<R, GENR, kFluxF<P, NS>, kFluxG<P, NS, GENR>>(p, s, d, q, h);
+    else
+      collide_fg<R, GENR, kFluxF<P, NS>, kFluxG<P, NS, GENR>>(p, s, d, q);
+    if constexpr (P::HDEV && NS) {
+#pragma clang fp contract(off)
+      R b[8];
+      h_store_basis(HRest<R>{s.P, s.jx, s.jy}, b);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) h[i] -= b[i];
+    }
+    bad |= owned && !isfinite(ph + ps + s.ux + s.uy);
+
+    // storage form
+    Two<S> w[9];
+    S wh[8];
+    if constexpr (P::SCALED) {
+      const unsigned site = uy_ * unx + ux_;
+      unsigned pw[9];
+      float amax = 0.f;
+      pack_fg(d, q, sc.f, sc.g, site, pw, amax);
+#pragma unroll
+      for (int i = 0; i < 9; ++i) {
+        const unsigned short lo = (unsigned short)(pw[i] & 0xffffu), hi = (unsigned short)(pw[i] >> 16);
+        w[i].a = __builtin_bit_cast(_Float16, lo);
+        w[i].b = __builtin_bit_cast(_Float16, hi);
+      }
+      if constexpr (NS) {
+        const bool odd = ux_ & 1u;
+        const unsigned key = (even ? site - (ux_ & 1u) : site) * 32u + 16u;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const float v = h[i] * sc.h;
+          amax = fmaxf(amax, fabsf(v));
+          const float o = even ? pair_lane(v) : 0.f;
+          const unsigned hw = halves_sr(even && odd ? o : v, even && odd ? v : o, key + unsigned(i));
+          const unsigned short s16 = (unsigned short)(even && odd ? hw >> 16 : hw & 0xffffu);
+          wh[i] = __builtin_bit_cast(_Float16, s16);
+        }
+      }
+      bad |= owned && !(amax <= kHalfMax);
+    } else {
+#pragma unroll
+      for (int i = 0; i < 9; ++i) {
+        w[i].a = S(d[i]);
+        w[i].b = S(q[i]);
+      }
+      if constexpr (NS) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) wh[k] = S(h[k]);
+      }
+    }
+
+    if (t == steps - 1) {  // last step: the sites of this block's interior to memory
+      if (owned) {
+        S *const dst = a.dst;
+        const long long rowb = (long long)y * (kPlanes * nx);
+#pragma unroll
+        for (int i = 0; i < 9; ++i)
+          *reinterpret_cast<Two<S> *>(dst + rowb + 2LL * (i * nx + x)) = w[i];
+        if constexpr (NS) {
+#pragma unroll
+          for (int k = 0; k < 8; ++k) dst[rowb + 18LL * nx + (long long)k * nx + x] = wh[k];
+        }
+        A *const r = a.dst_rest + ((long long)y * nx + x) * P::kRest;
+        r[0] = A(ph);
+        r[1] = A(ps);
+        if constexpr (P::HDEV && NS) {
+          r[2] = s.P;
+          r[3] = s.jx;
+          r[4] = s.jy;
+        }
+        if constexpr (!P::HDEV && NS) {
+          A *const u = ba.aux_out + ((long long)y * nx + x) * P::kAux;
+          u[0] = A(s.ux);
+          u[1] = A(s.uy);
+        }
+      }
+      break;
+    }
+
+#pragma unroll
+    for (int i = 1; i < 9; ++i) l_fg[i - 1][k0] = w[i];
+    if constexpr (NS) {
+#pragma unroll
+      for (int k = 0; k < 8; ++k) l_h[k][k0] = wh[k];
+    }
+    if constexpr (P::HDEV && NS) {
+      l_hr[0][k0] = s.P;
+      l_hr[1][k0] = s.jx;
+      l_hr[2][k0] = s.jy;
+    } else if constexpr (NS) {
+      uxp = s.ux;
+      uyp = s.uy;
+    }
+    decode(w[0], 0);
+    __syncthreads();
+
+    // next step: the state comes from LDS
+    const int cm = ly > 0 ? -B : 0, cp = ly < B - 1 ? B : 0;
+    decode(l_fg[0][k0 + dl], 1);
+    decode(l_fg[2][k0 + dr], 3);
+    decode(bot ? l_fg[3][k0] : l_fg[1][k0 + cm], 2);
+    decode(bot ? l_fg[6][k0] : l_fg[4][k0 + cm + dl], 5);
+    decode(bot ? l_fg[7][k0] : l_fg[5][k0 + cm + dr], 6);
+    decode(top ? l_fg[1][k0] : l_fg[3][k0 + cp], 4);
+    decode(top ? l_fg[4][k0] : l_fg[6][k0 + cp + dr], 7);
+    decode(top ? l_fg[5][k0] : l_fg[7][k0 + cp + dl], 8);
+    if constexpr (NS) {
+      decode_h(l_h[0][k0 + dl], 0);
+      decode_h(l_h[2][k0 + dr], 2);
+      decode_h(bot ? l_h[3][k0] : l_h[1][k0 + cm], 1);
+      decode_h(bot ? l_h[6][k0] : l_h[4][k0 + cm + dl], 4);
+      decode_h(bot ? l_h[7][k0] : l_h[5][k0 + cm + dr], 5);
+      decode_h(top ? l_h[1][k0] : l_h[3][k0 + cp], 3);
+      decode_h(top ? l_h[4][k0] : l_h[6][k0 + cp + dr], 6);
+      decode_h(top ? l_h[5][k0] : l_h[7][k0 + cp + dl], 7);
+    }
+    X = nine([&](int k) { return l_rest[t & 1][k].a; });
+    Y = nine([&](int k) { return l_rest[t & 1][k].b; });
+    if constexpr (P::HDEV && NS) {
+      HP = nine([&](int k) { return l_hr[0][k]; });
+      HX = nine([&](int k) { return l_hr[1][k]; });
+      HY = nine([&](int k) { return l_hr[2][k]; });
+    }
+  }
+  if (bad) *a.flag = 1;
 }
 
 // ------------------------------------------------------------ batched step
@@ -1794,7 +2208,7 @@ lbm_macro_fields_kernel(const SiteArgs<P> a, const Phys<typename P::R> p) {
     uyp = R(a.aux[aux_idx<P>(1, y, x, nx)]);
   }
   Front<R> s;
-  site_front<R, HAS_S>(p, s, vphi.c, sc[pl + k], vsig.c, gfx, gfy, lphi, gsx, gsy, h, php,
+  site_front<R, HAS_S, !P::SCALED>(p, s, vphi.c, sc[pl + k], vsig.c, gfx, gfy, lphi, gsx, gsy, h, php,
                        psp, uxp, uyp, Sxp, Syp);
   a.scratch[k] = double(s.phi);
   a.scratch[pl + k] = double(s.psi);
@@ -2097,9 +2511,19 @@ struct lbm_handle {
   bool genr, has_s, ns;
   bool resident;  // step stores with the default cache policy (cache_resident)
   int waves_resident;  // step wavefronts the device holds at once (0: unknown)
+  int block_plan;      // steps per launch of the block kernel (plan_block_steps)
+  int block_steps;     // the plan in use: 0 under a tile height set by the caller
   std::string kernel;  // the step kernel variant, as a profiler names it
   std::string err;
   double *fixed_scratch;  // this device's copy of the static read-back scratch
+};
+
+// One launch of the block kernel: its steps, and where it reads the previous
+// velocity and writes the new one.
+struct BlockLaunch {
+  int steps;
+  const void *aux_in;
+  void *aux_out;
 };
 
 // Step launches: compiled in both passes of this file (see lbm_f16_part).
@@ -2137,6 +2561,28 @@ int strips_of(const lbm_params &p) {
   return (p.nx + cols - 1) / cols;
 }
 
+template <class P>
+StepArgs<P> step_args(const lbm_handle *h, int cur) {
+  lbm_handle *hh = const_cast<lbm_handle *>(h);
+  StepArgs<P> a;
+  a.p = make_phys<typename P::R>(h->p);
+  a.sc = make_scales<P>(h->p);
+  a.src = static_cast<const typename P::S *>(pops(hh, cur));
+  a.src_rest = static_cast<const typename P::A *>(rest(hh, cur));
+  a.dst = static_cast<typename P::S *>(pops(hh, cur ^ 1));
+  a.dst_rest = static_cast<typename P::A *>(rest(hh, cur ^ 1));
+  a.aux = static_cast<typename P::A *>(auxp(hh));
+  a.flag = flagp(hh);
+  a.nx = h->p.nx;
+  a.ny = h->p.ny;
+  a.walls = h->p.walls_y;
+  a.nstrips = strips_of(h->p);
+  a.rows = h->rows;
+  a.tail_rows = 0;  // batched tiles come from the tile list
+  a.tail_h = 1;
+  return a;
+}
+
 // One step launch; with waves_per_cu set, instead the number of this
 // variant's wavefronts one compute unit holds at once.
 template <class P, int K, bool GENR, bool HAS_S, bool NS>
@@ -2148,20 +2594,7 @@ hipError_t launch_step(lbm_handle *h, int *waves_per_cu) {
     *waves_per_cu = blocks * P::kBlockWaves;
     return e;
   }
-  StepArgs<P> a;
-  a.p = make_phys<typename P::R>(h->p);
-  a.sc = make_scales<P>(h->p);
-  a.src = static_cast<const typename P::S *>(pops(h, h->cur));
-  a.src_rest = static_cast<const typename P::A *>(rest(h, h->cur));
-  a.dst = static_cast<typename P::S *>(pops(h, h->cur ^ 1));
-  a.dst_rest = static_cast<typename P::A *>(rest(h, h->cur ^ 1));
-  a.aux = static_cast<typename P::A *>(auxp(h));
-  a.flag = flagp(h);
-  a.nx = h->p.nx;
-  a.ny = h->p.ny;
-  a.walls = h->p.walls_y;
-  a.nstrips = strips_of(h->p);
-  a.rows = h->rows;
+  StepArgs<P> a = step_args<P>(h, h->cur);
   a.tail_rows = h->tail_rows;
   a.tail_h = h->tail_h;
   hipLaunchKernelGGL((lbm_step_kernel<P, K, GENR, HAS_S, NS>), dim3(step_grid<P>(a)),
@@ -2179,6 +2612,48 @@ hipError_t launch_step_prec(lbm_handle *h, int *waves_per_cu) {
                     : launch_step<P, K, true, false, true>(h, waves_per_cu);
   return h->has_s ? launch_step<P, K, false, true, true>(h, waves_per_cu)
                   : launch_step<P, K, false, false, true>(h, waves_per_cu);
+}
+
+// Blocks a launch of `steps` steps takes.
+int block_count(const lbm_params &p, int steps) {
+  const int hx = p.precision == LBM_FP16DEV ? block_halo_x<F16>(steps) : block_halo_x<F32>(steps);
+  const int w = kBlockSide - 2 * hx, t = kBlockSide - 2 * block_halo_y(steps);
+  const long long n = (long long)((p.nx + w - 1) / w) * ((p.ny + t - 1) / t);
+  return int(std::min<long long>(n, 1 << 30));
+}
+
+// A launch of the block kernel; with blocks_per_cu set, instead the number of
+// its workgroups one compute unit holds at once.
+template <class P, bool GENR, bool HAS_S, bool NS>
+hipError_t launch_block_as(lbm_handle *h, const BlockLaunch &l, int *blocks_per_cu) {
+  if (blocks_per_cu)
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(
+        blocks_per_cu, lbm_block_kernel<P, GENR, HAS_S, NS>, kBlockSide * kBlockSide, 0);
+  BlockArgs<P> b;
+  b.s = step_args<P>(h, h->cur);
+  b.s.aux = static_cast<typename P::A *>(const_cast<void *>(l.aux_in));
+  b.aux_out = static_cast<typename P::A *>(l.aux_out);
+  b.steps = l.steps;
+  const int w = kBlockSide - 2 * block_halo_x<P>(l.steps);
+  b.ntx = (h->p.nx + w - 1) / w;
+  b.ntiles = block_count(h->p, l.steps);
+  hipLaunchKernelGGL((lbm_block_kernel<P, GENR, HAS_S, NS>),
+                     dim3((b.ntiles + kXcds - 1) / kXcds * kXcds),
+                     dim3(kBlockSide * kBlockSide), 0, h->stream, b);
+  return hipGetLastError();
+}
+
+template <class P>
+hipError_t launch_block(lbm_handle *h, const BlockLaunch &l, int *blocks_per_cu) {
+  int *w = blocks_per_cu;
+  if (!h->ns)
+    return h->genr ? launch_block_as<P, true, false, false>(h, l, w)
+                   : launch_block_as<P, false, false, false>(h, l, w);
+  if (h->genr)
+    return h->has_s ? launch_block_as<P, true, true, true>(h, l, w)
+                    : launch_block_as<P, true, false, true>(h, l, w);
+  return h->has_s ? launch_block_as<P, false, true, true>(h, l, w)
+                  : launch_block_as<P, false, false, true>(h, l, w);
 }
 
 template <class P, int K, bool GENR, bool HAS_S, bool NS>
@@ -2214,6 +2689,7 @@ void launch_batch_prec(int c, int blocks, hipStream_t st, const void *desc,
 // tile-height independent with it.
 namespace lbm_f16_part {
 hipError_t step(lbm_handle *h, int *waves_per_cu);
+hipError_t block(lbm_handle *h, const BlockLaunch &l, int *blocks_per_cu);
 void batch(int c, int blocks, hipStream_t st, const void *desc, const void *tiles,
            const int *count, int k);
 }  // namespace lbm_f16_part
@@ -2223,6 +2699,9 @@ namespace lbm_f16_part {
 hipError_t step(lbm_handle *h, int *waves_per_cu) {
   return sites_per_lane(h->p) == 2 ? launch_step_prec<F16, 2>(h, waves_per_cu)
                                    : launch_step_prec<F16, 1>(h, waves_per_cu);
+}
+hipError_t block(lbm_handle *h, const BlockLaunch &l, int *blocks_per_cu) {
+  return launch_block<F16>(h, l, blocks_per_cu);
 }
 void batch(int c, int blocks, hipStream_t st, const void *desc, const void *tiles,
            const int *count, int k) {
@@ -2302,6 +2781,40 @@ hipError_t run_step(lbm_handle *h, int *waves_per_cu = nullptr) {
       return h->resident ? launch_step_prec<F32C, 1>(h, w) : launch_step_prec<F32, 1>(h, w);
     default: return lbm_f16_part::step(h, w);
   }
+}
+
+// Several steps of h in one launch (or, with blocks_per_cu set, the occupancy
+// of its block kernel).
+hipError_t run_block(lbm_handle *h, const BlockLaunch &l, int *blocks_per_cu = nullptr) {
+  switch (h->p.precision) {
+    case LBM_FP64: return launch_block<F64C>(h, l, blocks_per_cu);
+    case LBM_FP32: return launch_block<F32C>(h, l, blocks_per_cu);
+    default: return lbm_f16_part::block(h, l, blocks_per_cu);
+  }
+}
+
+// Time steps per launch of the block kernel, 0 where lbm_step_kernel is
+// faster.  A launch whose blocks all run at once costs its fixed part plus
+// its steps, and a second round of blocks doubles it, so the most steps are
+// taken whose blocks fit:
+//  * 3 (kBlockMaxSteps), if each block has a compute unit to itself (more steps leave 2 x 2
+//    sites of a block).  float32 96^2, 256 blocks: 2.65 us per step against
+//    3.36 with 2; 108^2, 324 blocks: 3.03 against 3.39 for float32, but
+//    5.46 against 3.84 for float64, of which a compute unit holds one block.
+//  * 2, if they are all resident: float64 160^2, 256 blocks, 3.98 us against
+//    6.33 with 1 and 7.9 for lbm_step_kernel; 176^2, 324 blocks, 6.67 against
+//    6.53 with 1.  float32 with the Navier-Stokes flow also gains with two
+//    rounds: 320x300, 960 blocks, 7.05 us against 7.68; 360x300, 1080
+//    blocks, 9.09 against 7.73.
+//  * 1, if they are all resident: float64 210^2, 225 blocks, 7.01 us against
+//    8.17; float16 176^2, 195 blocks, 6.86 against 8.39; 210^2, 270 blocks,
+//    11.2 against 8.56.
+int plan_block_steps(const lbm_handle *h, int cus, int resident) {
+  if (cus <= 0 || resident <= 0) return 0;
+  if (block_count(h->p, kBlockMaxSteps) <= cus) return kBlockMaxSteps;
+  const int rounds = h->p.precision == LBM_FP32 && h->ns ? 2 : 1;
+  if (block_count(h->p, 2) <= rounds * resident) return 2;
+  return block_count(h->p, 1) <= resident ? 1 : 0;
 }
 
 // Default tile height of a single simulation.  A step costs about one
@@ -2386,6 +2899,18 @@ int query_waves_resident(lbm_handle *h) {
     return 0;
   }
   return cus * per_cu;
+}
+
+// Steps per launch of h's block kernel on the current device.
+int query_block_steps(lbm_handle *h) {
+  int dev = 0, cus = 0, per_cu = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+      run_block(h, BlockLaunch{}, &per_cu) != hipSuccess) {
+    (void)hipGetLastError();
+    return 0;
+  }
+  return plan_block_steps(h, cus, cus * per_cu);
 }
 
 template <class P>
@@ -2519,6 +3044,7 @@ lbm_status lbm_create(const lbm_params *params, void *dev_ws, size_t ws_bytes,
   h->resident = cache_resident(*params);
   h->waves_resident = query_waves_resident(h);
   plan_tiles(h);
+  h->block_plan = h->block_steps = query_block_steps(h);
   h->kernel = kernel_name_of(h);
   int dev = -1;
   h->fixed_scratch = hipStreamGetDevice(h->stream, &dev) == hipSuccess ? fixed_scratch_of(dev)
@@ -2565,16 +3091,47 @@ lbm_status lbm_step(lbm_handle *h, int64_t nsteps) {
   if (!h) return LBM_EINVAL;
   if (nsteps < 0) return fail(h, LBM_EINVAL, "nsteps < 0");
   if (!h->valid) return fail(h, LBM_ESTATE, "no valid state");
-  for (int64_t t = 0; t < nsteps; ++t) {
-    hipError_t e = run_step(h);
+  bool launched = false;
+  auto after = [&](hipError_t e, int steps) {
     if (e != hipSuccess) {
       // the launches already enqueued still run: the state is no longer the
       // one before the call, nor a known number of steps past it
-      if (t > 0) h->valid = false;
+      if (launched) h->valid = false;
       return hip_check(h, e, "launching the step kernel");
     }
+    launched = true;
     h->cur ^= 1;
-    h->step += 1;
+    h->step += steps;
+    return LBM_OK;
+  };
+  int64_t left = nsteps;
+  if (h->block_steps > 0 && left > 1) {
+    // The blocks of one launch overlap, so a launch cannot update the
+    // previous velocity in place: launches write it alternately to the
+    // scratch planes and back, an even number of them.
+    const bool flips = h->ns && h->p.precision != LBM_FP16DEV;
+    void *const aux[2] = {auxp(h), flips ? scratch(h) : auxp(h)};
+    int64_t launches = (left + h->block_steps - 1) / h->block_steps;
+    if (flips && launches % 2) {
+      if (launches < left) {
+        ++launches;
+      } else {  // one step per launch: the odd step goes below, in place
+        --launches;
+      }
+    }
+    int64_t steps = h->block_steps == 1 ? launches : left;
+    left -= steps;
+    for (int64_t i = 0; i < launches; ++i) {
+      const int64_t rest = launches - i;
+      const BlockLaunch l = {int((steps + rest - 1) / rest), aux[i % 2], aux[(i + 1) % 2]};
+      const lbm_status st = after(run_block(h, l), l.steps);
+      if (st != LBM_OK) return st;
+      steps -= l.steps;
+    }
+  }
+  for (; left > 0; --left) {
+    const lbm_status st = after(run_step(h), 1);
+    if (st != LBM_OK) return st;
   }
   return LBM_OK;
 }
@@ -2784,9 +3341,11 @@ lbm_status lbm_set_tile_rows(lbm_handle *h, int32_t rows) {
   if (rows < 0 || rows > 4096) return fail(h, LBM_EINVAL, "rows out of range");
   if (rows == 0) {
     plan_tiles(h);
+    h->block_steps = h->block_plan;
   } else {
     h->rows = rows;
     taper_of(h);
+    h->block_steps = 0;
   }
   return LBM_OK;
 }
@@ -2817,28 +3376,6 @@ int class_of(const lbm_handle *h) {
   int group = int(h->p.precision);
   if (sites_per_lane(h->p) == 2) group = h->p.precision == LBM_FP32 ? 3 : 4;
   return group * 8 + (h->ns ? 0 : 4) + (h->genr ? 2 : 0) + (h->has_s ? 1 : 0);
-}
-
-template <class P>
-StepArgs<P> step_args(const lbm_handle *h, int cur) {
-  lbm_handle *hh = const_cast<lbm_handle *>(h);
-  StepArgs<P> a;
-  a.p = make_phys<typename P::R>(h->p);
-  a.sc = make_scales<P>(h->p);
-  a.src = static_cast<const typename P::S *>(pops(hh, cur));
-  a.src_rest = static_cast<const typename P::A *>(rest(hh, cur));
-  a.dst = static_cast<typename P::S *>(pops(hh, cur ^ 1));
-  a.dst_rest = static_cast<typename P::A *>(rest(hh, cur ^ 1));
-  a.aux = static_cast<typename P::A *>(auxp(hh));
-  a.flag = flagp(hh);
-  a.nx = h->p.nx;
-  a.ny = h->p.ny;
-  a.walls = h->p.walls_y;
-  a.nstrips = strips_of(h->p);
-  a.rows = h->rows;
-  a.tail_rows = 0;  // batched tiles come from the tile list
-  a.tail_h = 1;
-  return a;
 }
 
 size_t desc_size(int prec) {

@@ -83,6 +83,20 @@ __device__ __forceinline__ float ninth_of<float>(float x) {
   return __builtin_fmaf(x, 0x1.c71c72p-4f, x * -0x1.c71c72p-31f);
 }
 
+// a b + c in one fused multiply-add.  The compiler fuses a sum of two
+// products, a b + c d, around one of them, and which one depends on the code
+// around it (the order in which the operands were loaded, what else uses a
+// product).  So such sums are spelled out: a site's bits are then the same
+// in every kernel that steps it.
+template <class R>
+__device__ __forceinline__ R fused(R a, R b, R c) {
+  return __builtin_fma(a, b, c);
+}
+template <>
+__device__ __forceinline__ float fused<float>(float a, float b, float c) {
+  return __builtin_fmaf(a, b, c);
+}
+
 template <class R>
 __device__ __forceinline__ R rho_of(const Phys<R>& p, R phi) {
   return p.rhoB + p.drho * (phi - p.phiB);
@@ -109,8 +123,8 @@ struct Nine {
 template <class R>
 __device__ __forceinline__ void grad9(const Nine<R>& v, R& gx, R& gy) {
   const R third = R(1) / R(3), twelfth = R(1) / R(12);
-  gx = third * (v.cR - v.cL) + twelfth * ((v.nR - v.nL) + (v.mR - v.mL));
-  gy = third * (v.n - v.m) + twelfth * ((v.nR + v.nL) - (v.mR + v.mL));
+  gx = fused(third, v.cR - v.cL, twelfth * ((v.nR - v.nL) + (v.mR - v.mL)));
+  gy = fused(third, v.n - v.m, twelfth * ((v.nR + v.nL) - (v.mR + v.mL)));
 }
 
 // lap X = sum_i 2 w_i (X(x + c_i) - X(x)) / c_s^2, summed as differences
@@ -119,8 +133,8 @@ template <class R>
 __device__ __forceinline__ R lap9(const Nine<R>& v) {
   const R a = R(2) / R(3), b = R(1) / R(6);
   const R c = v.c;
-  return a * (((v.cR - c) + (v.cL - c)) + ((v.n - c) + (v.m - c))) +
-         b * (((v.nR - c) + (v.nL - c)) + ((v.mR - c) + (v.mL - c)));
+  return fused(a, ((v.cR - c) + (v.cL - c)) + ((v.n - c) + (v.m - c)),
+               b * (((v.nR - c) + (v.nL - c)) + ((v.mR - c) + (v.mL - c))));
 }
 
 // Everything the closures and the sources need at one site.
@@ -145,7 +159,7 @@ struct Front {
 template <class R>
 __device__ __forceinline__ void normal_delta(const Phys<R>& p, R phi, R gfx, R gfy, R& nx,
                                              R& ny, R& delta) {
-  const R gn = sqrt(gfx * gfx + gfy * gfy);
+  const R gn = sqrt(fused(gfx, gfx, gfy * gfy));
   const R inv = recip(gn + p.eps_n);
   nx = gfx * inv;
   ny = gfy * inv;
@@ -168,25 +182,26 @@ __device__ __forceinline__ void mass_flux(const Phys<R>& p, R phi, R gfx, R gfy,
 // Forces, closures and time differences at one site, from the stencils
 // (grad phi, lap phi, grad sigma, grad psi), sigma, the post-stream h_1..h_8
 // and the previous level (phi, psi, u, S).  Eqs. (8), (15), (16), (18),
-// (32a) read as rho u = sum c_i h_i + F/2, (32b) with K = 2/3.
-template <class R, bool HAS_S>
+// (32a) read as rho u = sum c_i h_i + F/2, (32b) with K = 2/3.  SY_FIRST:
+// which product of (Su + uS)_xy is fused.
+template <class R, bool HAS_S, bool SY_FIRST>
 __device__ __forceinline__ void site_front(const Phys<R>& p, Front<R>& s, R phi,
                                            R psi, R sig, R gfx, R gfy, R lphi,
                                            R gsx, R gsy, const R* h, R php,
                                            R psp, R uxp, R uyp, R Sxp, R Syp) {
   s.phi = phi;
   s.psi = psi;
-  const R gn2 = gfx * gfx + gfy * gfy;
+  const R gn2 = fused(gfx, gfx, gfy * gfy);
   normal_delta(p, phi, gfx, gfy, s.nx, s.ny, s.delta);
   const R qa = p.phiA - phi, qb = phi - p.phiB, qab = p.phiAB - phi - phi;
   s.a = p.c4W * qab;
   // capillary force sigma mu_phi grad phi plus Marangoni force, Eq. (18)
   const R muphi = p.cbulk * (qa * qb * qab) - p.cW * lphi;
-  const R sdp = gsx * gfx + gsy * gfy;
+  const R sdp = fused(gsx, gfx, gsy * gfy);
   const R rho = rho_of(p, phi);
   s.rho = rho;
-  s.Fx = sig * muphi * gfx + p.cW * (gn2 * gsx - sdp * gfx) + rho * p.gx;
-  s.Fy = sig * muphi * gfy + p.cW * (gn2 * gsy - sdp * gfy) + rho * p.gy;
+  s.Fx = fused(rho, p.gx, fused(sig * muphi, gfx, p.cW * (gn2 * gsx - sdp * gfx)));
+  s.Fy = fused(rho, p.gy, fused(sig * muphi, gfy, p.cW * (gn2 * gsy - sdp * gfy)));
   if (HAS_S) {
     mass_flux(p, phi, gfx, gfy, s.Sx, s.Sy);
     s.grx = p.drho * gfx;
@@ -220,18 +235,18 @@ __device__ __forceinline__ void site_front(const Phys<R>& p, Front<R>& s, R phi,
   if (HAS_S) {
     Txx -= s.Sx * ux;
     Tyy -= s.Sy * uy;
-    Txy -= R(0.5) * (s.Sx * uy + ux * s.Sy);
+    Txy -= R(0.5) * (SY_FIRST ? fused(ux, s.Sy, s.Sx * uy) : fused(s.Sx, uy, ux * s.Sy));
     Txxp -= Sxp * uxp;
     Tyyp -= Syp * uyp;
-    Txyp -= R(0.5) * (Sxp * uyp + uxp * Syp);
+    Txyp -= R(0.5) * fused(Sxp, uyp, uxp * Syp);
   }
   s.dTxx = Txx - Txxp;
   s.dTxy = Txy - Txyp;
   s.dTyy = Tyy - Tyyp;
   // Eq. (32b): P = c_s^2/(1-w0) [sum_{i!=0} h_i + u.grad rho/2
   //            - w0 (rho u - S).u/(2 c_s^2) + K/2 d_t(rho u.u - S.u)]
-  const R udr = ux * s.grx + uy * s.gry;
-  const R Au = (s.jx - s.Sx) * ux + (s.jy - s.Sy) * uy;
+  const R udr = fused(ux, s.grx, uy * s.gry);
+  const R Au = fused(s.jx - s.Sx, ux, (s.jy - s.Sy) * uy);
   s.P = R(0.6) * (sumh + R(0.5) * udr - R(2) / R(3) * Au +
                   R(1) / R(3) * (s.dTxx + s.dTyy));
   // Eq. (33): 1/s2 = 3 mu/rho + 1/2
@@ -332,18 +347,18 @@ __device__ __forceinline__ void collide_flow(R* h, const Front<R>& s, R s3, R s4
   R m3 = (h[0] + h[2]) + m8, m4 = (h[1] + h[3]) + m8;
   const R ux = s.ux, uy = s.uy;
   const R Ax = s.jx - s.Sx, Ay = s.jy - s.Sy;
-  const R Au = Ax * ux + Ay * uy;
-  const R B = ux * s.grx + uy * s.gry;
+  const R Au = fused(Ax, ux, Ay * uy);
+  const R B = fused(ux, s.grx, uy * s.gry);
   const R mxx = s.dTxx + third_of(R(2) * ux * s.grx);
   const R myy = s.dTyy + third_of(R(2) * uy * s.gry);
-  const R mxy = s.dTxy + third_of(ux * s.gry + uy * s.grx);
+  const R mxy = s.dTxy + third_of(fused(ux, s.gry, uy * s.grx));
   const R s2 = s.s2h, h2 = R(1) - R(0.5) * s2;
   const R h3 = R(1) - R(0.5) * s3, h4 = R(1) - R(0.5) * s4;
   m1 = m1 + s.Fx;
   m2 = m2 + s.Fy;
   m3 = m3 - s2 * (m3 - (s.P + Ax * ux)) + h2 * (third_of(B) + mxx);
   m4 = m4 - s2 * (m4 - (s.P + Ay * uy)) + h2 * (third_of(B) + myy);
-  m5 = m5 - s2 * (m5 - R(0.5) * (Ax * uy + Ay * ux)) + h2 * mxy;
+  m5 = m5 - s2 * (m5 - R(0.5) * fused(Ax, uy, Ay * ux)) + h2 * mxy;
   m6 = m6 - s3 * (m6 - third_of(s.jx)) + h3 * third_of(s.Fx);
   m7 = m7 - s3 * (m7 - third_of(s.jy)) + h3 * third_of(s.Fy);
   m8 = m8 - s4 * (m8 - third_of(s.P + Au)) + h4 * (ninth_of(B) + third_of(mxx + myy));
@@ -380,33 +395,34 @@ __device__ __forceinline__ void site_front_prescribed(const Phys<R>& p, Front<R>
 }
 
 // The phase-field and surfactant collisions of one site (9 populations each).
-template <class R, bool GENR>
+// The sources 3 d_t(X u) + flux are fused around the flux product in f if
+// FLUX_F, in g if FLUX_G, else around the time difference.
+template <class R, bool GENR, bool FLUX_F, bool FLUX_G>
 __device__ __forceinline__ void collide_fg(const Phys<R>& p, const Front<R>& s, R* f, R* g) {
+  auto source = [](bool flux_first, R dt, R k, R n) {
+    return flux_first ? fused(k, n, R(3) * dt) : fused(R(3), dt, k * n);
+  };
   // phase field: V = 3 d_t(phi u) + delta n  (Eq. (22))
-  collide_cde(f, s.phi, s.ux, s.uy, R(3) * s.dpux + s.delta * s.nx,
-              R(3) * s.dpuy + s.delta * s.ny, p.s1f, p.s2f, p.s3f, p.s4f);
+  collide_cde(f, s.phi, s.ux, s.uy, source(FLUX_F, s.dpux, s.delta, s.nx),
+              source(FLUX_F, s.dpuy, s.delta, s.ny), p.s1f, p.s2f, p.s3f, p.s4f);
   // surfactant: V = 3 d_t(psi u) + j, j = r a psi n - (r-1)(n.grad psi) n;
   // at r = 1, j = a psi n exactly as in Eq. (26)
-  R jx, jy;
+  R k;
   if (GENR) {
-    const R ndg = s.nx * s.gpx + s.ny * s.gpy;
-    const R k = p.r * s.a * s.psi - p.rm1 * ndg;
-    jx = k * s.nx;
-    jy = k * s.ny;
+    const R ndg = fused(s.nx, s.gpx, s.ny * s.gpy);
+    k = p.r * s.a * s.psi - p.rm1 * ndg;
   } else {
-    const R k = s.a * s.psi;
-    jx = k * s.nx;
-    jy = k * s.ny;
+    k = s.a * s.psi;
   }
-  collide_cde(g, s.psi, s.ux, s.uy, R(3) * s.dqux + jx, R(3) * s.dquy + jy,
-              p.s1g, p.s2g, p.s3g, p.s4g);
+  collide_cde(g, s.psi, s.ux, s.uy, source(FLUX_G, s.dqux, k, s.nx),
+              source(FLUX_G, s.dquy, k, s.ny), p.s1g, p.s2g, p.s3g, p.s4g);
 }
 
 // The three collisions of one site.  f, g: 9 populations; h: h_1..h_8.
-template <class R, bool GENR>
+template <class R, bool GENR, bool FLUX_F, bool FLUX_G>
 __device__ __forceinline__ void collide_site(const Phys<R>& p, const Front<R>& s,
                                              R* f, R* g, R* h) {
-  collide_fg<R, GENR>(p, s, f, g);
+  collide_fg<R, GENR, FLUX_F, FLUX_G>(p, s, f, g);
   collide_flow(h, s, p.s3h, p.s4h);
 }
 
