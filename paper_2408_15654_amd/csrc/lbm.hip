@@ -63,6 +63,8 @@ constexpr int kPlanes = 26;
 constexpr int kScratch = 8;
 constexpr int kReduceBlocks = 1024;
 constexpr int kReduceVals = 8;
+constexpr int kMomentVals = 7;               // lbm_reduce_kernel's values,
+constexpr unsigned kMomentMaxes = 1u << 5 | 1u << 6;  // of which 5 and 6 are maxima
 
 // Minimum waves per SIMD the compiler schedules the step kernel for.  The
 // value steers the instruction scheduler as much as the register budget:
@@ -2263,16 +2265,57 @@ lbm_reduce_kernel(const double *scratch, long long plane, long long n,
   }
 }
 
-__global__ void __launch_bounds__(64)
-lbm_reduce_final_kernel(const double *partials, int nblocks, double *out) {
-  if (threadIdx.x >= 7) return;
-  const int j = threadIdx.x;
-  double v = partials[j];
-  for (int b = 1; b < nblocks; ++b) {
-    const double q = partials[b * kReduceVals + j];
-    v = (j == 5 || j == 6) ? fmax(v, q) : v + q;
+// Adds the blocks' partials in block order (maxima for the values of MAXES),
+// deterministically, and appends *flag (if given) as a double.  One dependent
+// chain of at most kReduceBlocks additions per value: what bounds it is how
+// soon the next operand is there, so all partials are first brought into LDS
+// by the whole workgroup (walking them from memory, one round trip per few
+// additions, took 168 us for 1024 blocks; this takes 16 us, 4 us for 128).  The sums and
+// the maxima are walked by different wavefronts.
+constexpr int kFinalThreads = 256;
+template <int NV, int STRIDE, unsigned MAXES>
+__global__ void __launch_bounds__(kFinalThreads)
+lbm_final_kernel(const double *partials, int nblocks, const int *flag, double *out) {
+  __shared__ double col[NV][kReduceBlocks + 2];  // padded: columns start in different banks
+#pragma unroll 8
+  for (int i = int(threadIdx.x); i < nblocks * STRIDE; i += kFinalThreads) {
+    const double v = partials[i];
+    if (i % STRIDE < NV) col[i % STRIDE][i / STRIDE] = v;
   }
-  out[j] = v;
+  __syncthreads();
+  const int j = int(threadIdx.x) & (kWave - 1), wv = int(threadIdx.x) / kWave;
+  if (j >= NV || wv > 1 || (wv == 1) != bool(MAXES >> j & 1u)) return;
+  auto walk = [&](auto add) {
+    constexpr int U = 32;  // operands on their way while the last ones are added
+    double v = col[j][0], q[U];
+    int b = 1;
+    if (b + U <= nblocks) {
+#pragma unroll
+      for (int k = 0; k < U; ++k) q[k] = col[j][b + k];
+      for (b += U; b + U <= nblocks; b += U) {
+        double r[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) r[k] = col[j][b + k];
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+          v = add(v, q[k]);
+          q[k] = r[k];
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < U; ++k) v = add(v, q[k]);
+    }
+    for (; b < nblocks; ++b) v = add(v, col[j][b]);
+    return v;
+  };
+  out[j] = wv == 0 ? walk([](double x, double y) { return x + y; })
+                   : walk([](double x, double y) { return fmax(x, y); });
+  if (flag && j == 0) out[NV] = double(*flag);
+}
+
+// Blocks of a reduction over n sites: those beyond the sites would add zeros.
+int reduce_blocks(long long n) {
+  return int(std::min<long long>(kReduceBlocks, (n + 255) / 256));
 }
 
 // Shape diagnostics of fluid A from the float64 phi of scratch plane 0:
@@ -2328,16 +2371,6 @@ lbm_shape_kernel(const double *phi, int nx, int ny, int walls, double phiA, doub
     for (int q = 1; q < 256 / kWave; ++q) v += lds[j][q];
     partials[blockIdx.x * kShapeVals + j] = v;
   }
-}
-
-// Sums of nvals partial columns over nblocks, in block order.
-__global__ void __launch_bounds__(64)
-lbm_sum_final_kernel(const double *partials, int nblocks, int nvals, double *out) {
-  if (int(threadIdx.x) >= nvals) return;
-  const int j = threadIdx.x;
-  double v = partials[j];
-  for (int b = 1; b < nblocks; ++b) v += partials[b * nvals + j];
-  out[j] = v;
 }
 
 // ------------------------------------------------------------------ host
@@ -2995,6 +3028,24 @@ hipError_t run_init(lbm_handle *h) {
   }
 }
 
+// The moments of the read-back planes at sc into res (kMomentVals values,
+// and the sticky flag after them if given).
+hipError_t launch_moments(lbm_handle *h, const double *sc, long long plane, double *part,
+                          const int *flag, double *res) {
+  const long long n = (long long)h->p.nx * h->p.ny;
+  const int blocks = reduce_blocks(n);
+  hipLaunchKernelGGL(lbm_reduce_kernel, dim3(blocks), dim3(256), 0, h->stream, sc, plane, n,
+                     make_phys<double>(h->p), part);
+  hipLaunchKernelGGL((lbm_final_kernel<kMomentVals, kReduceVals, kMomentMaxes>), dim3(1),
+                     dim3(kFinalThreads), 0, h->stream, (const double *)part, blocks, flag, res);
+  return hipGetLastError();
+}
+
+lbm_status nonfinite(lbm_handle *h) {
+  h->valid = false;
+  return fail(h, LBM_ENONFINITE, "the device produced a non-finite value");
+}
+
 // Reads the sticky device flag (synchronising); marks the state invalid.
 lbm_status check_flag(lbm_handle *h) {
   int flag = 0;
@@ -3002,11 +3053,7 @@ lbm_status check_flag(lbm_handle *h) {
                                 h->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
   if (e != hipSuccess) return hip_check(h, e, "reading the non-finite flag");
-  if (flag) {
-    h->valid = false;
-    return fail(h, LBM_ENONFINITE, "the device produced a non-finite value");
-  }
-  return LBM_OK;
+  return flag ? nonfinite(h) : LBM_OK;
 }
 
 }  // namespace
@@ -3160,24 +3207,18 @@ lbm_status lbm_moments(lbm_handle *h, lbm_moments_t *out) {
   if (!h) return LBM_EINVAL;
   if (!out) return fail(h, LBM_EINVAL, "out is NULL");
   if (!h->valid) return fail(h, LBM_ESTATE, "no valid state");
-  lbm_status st = check_flag(h);
-  if (st != LBM_OK) return st;
   hipError_t e = run_macros(h);
   if (e != hipSuccess) return hip_check(h, e, "launching read-back kernels");
-  const Phys<double> p = make_phys<double>(h->p);
   double *part = partials(h);
-  const long long n = (long long)h->p.nx * h->p.ny;
-  hipLaunchKernelGGL(lbm_reduce_kernel, dim3(kReduceBlocks), dim3(256), 0, h->stream,
-                     (const double *)scratch(h), h->L.plane, n, p, part);
-  hipLaunchKernelGGL(lbm_reduce_final_kernel, dim3(1), dim3(64), 0, h->stream,
-                     (const double *)part, kReduceBlocks, part + kReduceBlocks * kReduceVals);
-  e = hipGetLastError();
+  double *res = part + kReduceBlocks * kReduceVals;
+  e = launch_moments(h, scratch(h), h->L.plane, part, flagp(h), res);
   double v[kReduceVals];
+  static_assert(kMomentVals + 1 <= kReduceVals, "the flag follows the moments");
   if (e == hipSuccess)
-    e = hipMemcpyAsync(v, part + kReduceBlocks * kReduceVals, sizeof v,
-                       hipMemcpyDeviceToHost, h->stream);
+    e = hipMemcpyAsync(v, res, sizeof v, hipMemcpyDeviceToHost, h->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
   if (e != hipSuccess) return hip_check(h, e, "reducing");
+  if (v[kMomentVals] != 0.0) return nonfinite(h);
   out->step = h->step;
   out->sum_phi = v[0];
   out->sum_psi = v[1];
@@ -3208,44 +3249,42 @@ lbm_status lbm_moments_async(lbm_handle *h, double *dev_out) {
   hipError_t e = run_macros(h, base, plane);
   if (e != hipSuccess) return hip_check(h, e, "launching read-back kernels");
   double *part = base + kScratch * kFixedSites;
-  const Phys<double> p = make_phys<double>(h->p);
-  hipLaunchKernelGGL(lbm_reduce_kernel, dim3(kReduceBlocks), dim3(256), 0, h->stream,
-                     (const double *)base, plane, n, p, part);
-  hipLaunchKernelGGL(lbm_reduce_final_kernel, dim3(1), dim3(64), 0, h->stream,
-                     (const double *)part, kReduceBlocks, dev_out);
-  return hip_check(h, hipGetLastError(), "launching the reductions");
+  return hip_check(h, launch_moments(h, base, plane, part, nullptr, dev_out),
+                   "launching the reductions");
 }
 
 lbm_status lbm_shape(lbm_handle *h, lbm_shape_t *out) {
   if (!h) return LBM_EINVAL;
   if (!out) return fail(h, LBM_EINVAL, "out is NULL");
   if (!h->valid) return fail(h, LBM_ESTATE, "no valid state");
-  lbm_status st = check_flag(h);
-  if (st != LBM_OK) return st;
   hipError_t e = run_macros(h);
   if (e != hipSuccess) return hip_check(h, e, "launching read-back kernels");
   const lbm_params &p = h->p;
   const double *phi = scratch(h);
   double *part = partials(h);
   double *res = part + kReduceBlocks * kShapeVals;
+  const int blocks = reduce_blocks((long long)p.nx * p.ny);
   auto pass = [&](int which, double cx, double cy, double *v) -> hipError_t {
     if (which == 1)
-      hipLaunchKernelGGL(lbm_shape_kernel<1>, dim3(kReduceBlocks), dim3(256), 0, h->stream,
+      hipLaunchKernelGGL(lbm_shape_kernel<1>, dim3(blocks), dim3(256), 0, h->stream,
                          phi, p.nx, p.ny, p.walls_y, p.phiA, p.phiB, cx, cy, part);
     else
-      hipLaunchKernelGGL(lbm_shape_kernel<2>, dim3(kReduceBlocks), dim3(256), 0, h->stream,
+      hipLaunchKernelGGL(lbm_shape_kernel<2>, dim3(blocks), dim3(256), 0, h->stream,
                          phi, p.nx, p.ny, p.walls_y, p.phiA, p.phiB, cx, cy, part);
-    hipLaunchKernelGGL(lbm_sum_final_kernel, dim3(1), dim3(64), 0, h->stream,
-                       (const double *)part, kReduceBlocks, kShapeVals, res);
+    hipLaunchKernelGGL((lbm_final_kernel<kShapeVals, kShapeVals, 0u>), dim3(1),
+                       dim3(kFinalThreads), 0, h->stream, (const double *)part, blocks,
+                       (const int *)flagp(h), res);
     hipError_t e2 = hipGetLastError();
     if (e2 == hipSuccess)
-      e2 = hipMemcpyAsync(v, res, sizeof(double) * kShapeVals, hipMemcpyDeviceToHost, h->stream);
+      e2 = hipMemcpyAsync(v, res, sizeof(double) * (kShapeVals + 1), hipMemcpyDeviceToHost,
+                          h->stream);
     if (e2 == hipSuccess) e2 = hipStreamSynchronize(h->stream);
     return e2;
   };
-  double s1[kShapeVals], s2[kShapeVals];
+  double s1[kShapeVals + 1], s2[kShapeVals + 1];  // the flag follows the values
   e = pass(1, 0.0, 0.0, s1);
   if (e != hipSuccess) return hip_check(h, e, "shape pass 1");
+  if (s1[kShapeVals] != 0.0) return nonfinite(h);
   const double area = s1[0];
   if (!(area > 0.0)) return fail(h, LBM_EINVAL, "no fluid A in the domain");
   auto circ = [](double c, double s, int n) {
