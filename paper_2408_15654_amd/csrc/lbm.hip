@@ -454,6 +454,23 @@ __device__ __forceinline__ void h_arrival_basis(const Nine<R> &P, const Nine<R> 
   b[7] = top ? hb(d, P.c, -1, jx.c, 1, jy.c) : hb(d, P.nL, 1, jx.nL, -1, jy.nL);
 }
 
+// The same where (bot, top) is the same on every lane: wall rows are rare, so
+// they are branched to.
+template <class R>
+__device__ __forceinline__ void source_offsets_row(const Nine<R> &v, bool bot, bool top, R *e) {
+  const R c = v.c;
+  e[0] = R(0);
+  e[1] = v.cL - c;
+  e[3] = v.cR - c;
+  e[2] = v.m - c;
+  e[5] = v.mL - c;
+  e[6] = v.mR - c;
+  e[4] = v.n - c;
+  e[7] = v.nR - c;
+  e[8] = v.nL - c;
+  if (bot) e[2] = e[5] = e[6] = R(0);
+  if (top) e[4] = e[7] = e[8] = R(0);
+}
 template <class R>
 __device__ __forceinline__ void source_offsets(const Nine<R> &v, bool bot, bool top, R *e) {
   const R c = v.c;
@@ -1940,6 +1957,363 @@ lbm_block_kernel(const BlockArgs<P> ba) {
   if (bad) *a.flag = 1;
 }
 
+// ------------------------------------------------- two steps per launch, rows
+
+// Two-step kernel (large grids, float32 and float64 storage, Navier-Stokes
+// flow): a wavefront walks down a strip of columns as lbm_step_kernel's does,
+// one column per lane, and takes each row through two time steps.  The first
+// step's row j goes to LDS; the second step pulls rows j-2, j-1, j of it to
+// rebuild row j-1, and stores row j-2.  The populations so cross memory once
+// per two steps.  A step reaches two sites in every direction: 56 of the 64
+// columns are stored, and the first step walks two more rows at each end.
+//
+// What bounds it: vector issue (about 1450 instructions per row of two
+// steps; 77% of the issue slots of 2.4 GHz are used on 2048^2 float32), where
+// a step per launch is bound by memory (1.0 GB per step).  Two float32
+// wavefronts share a SIMD (190-202 registers, 18 KB of LDS each), one float64
+// wavefront has it alone.  Two columns per lane need 430 registers for
+// float32: 135 us per step on 2048^2 against 132.
+// Measured per step on MI355X, lbm_step_kernel -> this: float32 1024^2
+// 47.0 -> 37.0 us, 2048x1024 97.9 -> 69.1, 2048^2 196 -> 132, 4096^2
+// 799 -> 485; float64 1023x769 77.4 -> 55.6, 2048^2 362 -> 229.
+
+// LDS of one wavefront: the rows of the first step's state that the second
+// still has to pull from, in rings over the rows.  Populations that stream
+// up are pulled last and kept longest; one that a wall sends back is pulled
+// from its own row instead.  Columns are offset by 1, so that the shifted
+// reads of the edge lanes stay inside a row (their values are not used).
+template <class P>
+struct PairLds {
+  using S = typename P::S;
+  static constexpr int W = kWave + 2;
+  Two<S> up[3][3][W];   // (f, g)_2, 5, 6 of rows j-2 .. j
+  Two<S> mid[2][3][W];  // (f, g)_0, 1, 3 of rows j-1, j
+  Two<S> dn[2][3][W];   // (f, g)_4, 7, 8 of rows j-1, j
+  S hup[4][3][W];       // h_2, 5, 6 of rows j-3 .. j
+  S hmid[3][2][W];      // h_1, 3 of rows j-2 .. j
+  S hdn[3][3][W];       // h_4, 7, 8 of rows j-2 .. j
+};
+
+constexpr int kPairHalo = 4;                       // columns on each side
+constexpr int kPairCols = kWave - 2 * kPairHalo;   // columns stored
+
+template <class P>
+struct PairArgs {
+  StepArgs<P> s;
+  typename P::A *aux_out;  // new previous velocity (s.aux is read by several wavefronts)
+  int tiles;               // per XCD
+};
+
+// phi, psi, sigma of one site.
+template <class R>
+struct Scalars {
+  R ph, ps, sg;
+};
+
+// Rows [y0, y1) of one strip, two steps, by one wavefront.
+template <class P, bool GENR, bool HAS_S>
+__device__ __forceinline__ void pair_tile(const StepArgs<P> &a, typename P::A *aux_out,
+                                          const int strip, const int y0, const int y1,
+                                          PairLds<P> &ls) {
+  using R = typename P::R;
+  using S = typename P::S;
+  using A = typename P::A;
+  static_assert(!P::SCALED, "float64 or float32 storage");
+  const int lane = threadIdx.x & (kWave - 1);
+  const int nx = a.nx, ny = a.ny, walls = a.walls;
+  const int x0 = strip * kPairCols;
+  const int wl = min(kPairCols, nx - x0);
+  const bool interior = lane >= kPairHalo && lane < kPairHalo + wl;
+  int xl = x0 - kPairHalo + min(lane, wl + 2 * kPairHalo - 1);
+  xl %= nx;
+  if (xl < 0) xl += nx;
+  const unsigned xc = unsigned(xl);
+  const unsigned xcm = xl == 0 ? unsigned(nx - 1) : xc - 1;
+  const unsigned xcp = xl == nx - 1 ? 0u : xc + 1;
+  constexpr unsigned ES = sizeof(S), EA = sizeof(A);
+  const ColOff co = {xc * 2 * ES, xcm * 2 * ES, xcp * 2 * ES, xc * ES, xcm * ES, xcp * ES};
+  const unsigned brest = xc * P::kRest * EA, baux = xc * P::kAux * EA;
+  const unsigned nsites = unsigned(nx) * unsigned(ny);
+  const unsigned nxb = unsigned(nx) * 2 * ES, nxh = unsigned(nx) * ES, hb = 9u * nxb;
+  const unsigned rows_s = unsigned(kPlanes) * nxh;
+  const unsigned rrow = unsigned(nx) * P::kRest * EA, arow = unsigned(nx) * P::kAux * EA;
+  const rsrc_t rsrc = make_rsrc(a.src, unsigned(kPlanes) * nsites * ES);
+  const rsrc_t rdst = make_rsrc(a.dst, unsigned(kPlanes) * nsites * ES);
+  const rsrc_t rrest = make_rsrc(a.src_rest, unsigned(P::kRest) * nsites * EA);
+  const rsrc_t rdrest = make_rsrc(a.dst_rest, unsigned(P::kRest) * nsites * EA);
+  const rsrc_t raux = make_rsrc(a.aux, unsigned(P::kAux) * nsites * EA);
+  const rsrc_t rauxo = make_rsrc(aux_out, unsigned(P::kAux) * nsites * EA);
+  const Phys<R> &p = a.p;
+  const Scales<P> &sc = a.sc;
+  const int c = lane + 1;  // this lane's column in an LDS row
+
+  // Row numbers run two past each end of the tile and may lie outside the
+  // grid: wrapped, or clamped between walls (such rows are never used).
+  auto rest_at = [&](int r, R &X, R &Y) {
+    A u, v;
+    PairIO<A>::load(rrest, brest, unsigned(wrap_row(r, ny, walls)) * rrow, u, v);
+    X = R(u);
+    Y = R(v);
+  };
+  auto load_fg = [&](int r, R *d, R *q) {
+    Pull<P>::fg(rsrc, nxb, row_offsets(wrap_row(r, ny, walls), ny, walls, rows_s), co, sc, d, q);
+  };
+  auto load_row = [&](int r, R *h, R &ux, R &uy) {
+    const int y = wrap_row(r, ny, walls);
+    Pull<P>::h(rsrc, hb, nxh, row_offsets(y, ny, walls, rows_s), co, sc.hi, h);
+    A u, v;
+    PairIO<A>::load(raux, baux, unsigned(y) * arow, u, v);
+    ux = R(u);
+    uy = R(v);
+  };
+  auto at_bottom = [&](int r) { return walls && r == 0; };
+  auto at_top = [&](int r) { return walls && r == ny - 1; };
+  auto window = [](R m, R v, R n) { return window_k<1, 0>(&m, &v, &n); };
+  // phi, psi, sigma of row r from its pulled deviations and the previous
+  // level's phi (X) and psi (Y) of rows r-1, r, r+1
+  auto rebuild = [&](int r, R Xm, R Xc, R Xn, R Ym, R Yc, R Yn, R *d, R *q) {
+    const bool bot = at_bottom(r), top = at_top(r);
+    Scalars<R> v;
+    R e[9];
+    source_offsets_row(window(Xm, Xc, Xn), bot, top, e);
+    v.ph = restream(d, e, Xc);
+    source_offsets_row(window(Ym, Yc, Yn), bot, top, e);
+    v.ps = restream(q, e, Yc);
+    v.sg = sigma_of(p, v.ps);
+    return v;
+  };
+  // collision of row r, in place on d, q, h: from the level's scalars of rows
+  // r-1, r, r+1 and the previous level's phi of the same rows, psi and u
+  auto collide_row = [&](int r, const Scalars<R> &m, const Scalars<R> &v, const Scalars<R> &n,
+                         R Xm, R Xc, R Xn, R Yc, R uxp, R uyp, R *d, R *q, R *h, R &ux, R &uy) {
+    R Sxp = R(0), Syp = R(0);
+    if constexpr (HAS_S) {
+      R fx, fy;
+      grad9(window(Xm, Xc, Xn), fx, fy);
+      mass_flux(p, Xc, fx, fy, Sxp, Syp);
+    }
+    wall_terms(at_bottom(r), at_top(r), rho_of(p, Xc), p.uwb, p.uwt, h);
+    const Nine<R> vphi = window(m.ph, v.ph, n.ph), vsig = window(m.sg, v.sg, n.sg);
+    R gfx, gfy, gsx, gsy;
+    grad9(vphi, gfx, gfy);
+    grad9(vsig, gsx, gsy);
+    const R lphi = lap9(vphi);
+    Front<R> s;
+    site_front<R, HAS_S, true>(p, s, v.ph, v.ps, v.sg, gfx, gfy, lphi, gsx, gsy, h, Xc, Yc, uxp,
+                               uyp, Sxp, Syp);
+    if constexpr (GENR) {
+      grad9(window(m.ps, v.ps, n.ps), s.gpx, s.gpy);
+    } else {
+      s.gpx = s.gpy = R(0);
+    }
+    collide_site<R, GENR, kFluxF<P, true>, kFluxG<P, true, GENR>>(p, s, d, q, h);
+    ux = s.ux;
+    uy = s.uy;
+  };
+
+  // Memory: X, Y are phi, psi of rows j-1 .. j+2; dn, qn the raw deviations
+  // of row j+1; hr, uxr, uyr h and u of row j.
+  R X0, X1, X2, X3, Y0, Y1, Y2, Y3;
+  R dc[9], qc[9], dn[9], qn[9], hr[8], uxr, uyr;
+  // First step's level: scalars of rows j-1 (m), j (v) and deviations of row
+  // j; after its collision phi, psi, u of rows j-1, j-2 and phi of row j-3,
+  // the previous level of the second step.
+  Scalars<R> m1, v1;
+  R f1 = R(0), f2 = R(0), f3 = R(0), s1 = R(0), s2 = R(0);
+  R ux1 = R(0), uy1 = R(0), ux2 = R(0), uy2 = R(0);
+  // Second step's level: scalars of rows j-3 (m), j-2 (v), deviations of j-2.
+  Scalars<R> m2 = {R(0), R(0), R(0)}, v2 = {R(0), R(0), R(0)};
+  R dd[9] = {}, qd[9] = {};
+  const int j0 = y0 - 2;
+  {
+    R dt[9], qt[9], Xa, Ya;
+    rest_at(j0 - 1, X0, Y0);
+    rest_at(j0, X1, Y1);
+    rest_at(j0 + 1, X2, Y2);
+    rest_at(j0 + 2, X3, Y3);
+    load_fg(j0, dc, qc);
+    rest_at(j0 - 2, Xa, Ya);
+    load_fg(j0 - 1, dt, qt);
+    load_fg(j0 + 1, dn, qn);
+    load_row(j0, hr, uxr, uyr);
+    v1 = rebuild(j0, X0, X1, X2, Y0, Y1, Y2, dc, qc);
+    m1 = rebuild(j0 - 1, Xa, X0, X1, Ya, Y0, Y1, dt, qt);
+  }
+  // halo lanes' stores are dropped by the hardware, as in step_tile
+  const unsigned cs_p = interior ? co.p0 : kDropped, cs_h = interior ? co.h0 : kDropped;
+  const unsigned brest_s = interior ? brest : kDropped, baux_s = interior ? baux : kDropped;
+  bool bad = false;
+  int r3 = 0, r2 = 0, r4 = 0;  // ring slots of row j
+
+  // Row j of the first step; then of the second, row j-1 rebuilt (if second)
+  // and row j-2 collided and stored (if STORE).
+  auto row = [&](int j, auto store, bool second) {
+    constexpr bool STORE = decltype(store)::value;
+    const int r3b = r3 == 0 ? 2 : r3 - 1, r3c = r3b == 0 ? 2 : r3b - 1;  // rows j-1, j-2
+    const int r2b = r2 ^ 1, r4b = (r4 + 2) & 3, r4c = (r4 + 1) & 3;      // j-1; j-2, j-3
+    Scalars<R> n1 = rebuild(j + 1, X1, X2, X3, Y1, Y2, Y3, dn, qn);
+    R h[8], dk[9], qk[9], X4, Y4;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) h[i] = hr[i];
+#pragma unroll
+    for (int i = 0; i < 9; ++i) {
+      dk[i] = dn[i];
+      qk[i] = qn[i];
+    }
+    const R uxp = uxr, uyp = uyr;
+    rest_at(j + 3, X4, Y4);
+    load_fg(j + 2, dn, qn);
+    load_row(j + 1, hr, uxr, uyr);
+    // at a wall the stencils' row beyond it is the wall row itself
+    if (at_bottom(j)) m1 = v1;
+    if (at_top(j)) n1 = v1;
+    R ux, uy;
+    collide_row(j, m1, v1, n1, X0, X1, X2, Y1, uxp, uyp, dc, qc, h, ux, uy);
+    bad |= interior && j >= y0 && j < y1 && !isfinite(v1.ph + v1.ps + ux + uy);
+    auto w = [&](int i) { return Two<S>{S(dc[i]), S(qc[i])}; };
+    ls.up[r3][0][c] = w(2);
+    ls.up[r3][1][c] = w(5);
+    ls.up[r3][2][c] = w(6);
+    ls.mid[r2][0][c] = w(0);
+    ls.mid[r2][1][c] = w(1);
+    ls.mid[r2][2][c] = w(3);
+    ls.dn[r2][0][c] = w(4);
+    ls.dn[r2][1][c] = w(7);
+    ls.dn[r2][2][c] = w(8);
+    ls.hup[r4][0][c] = S(h[1]);
+    ls.hup[r4][1][c] = S(h[4]);
+    ls.hup[r4][2][c] = S(h[5]);
+    ls.hmid[r3][0][c] = S(h[0]);
+    ls.hmid[r3][1][c] = S(h[2]);
+    ls.hdn[r3][0][c] = S(h[3]);
+    ls.hdn[r3][1][c] = S(h[6]);
+    ls.hdn[r3][2][c] = S(h[7]);
+
+    Scalars<R> n2 = {R(0), R(0), R(0)};
+    R de[9], qe[9];
+    if (second) {
+      const bool bot = at_bottom(j - 1), top = at_top(j - 1);
+      auto get = [&](const Two<S> *row, int i) {
+        const Two<S> t = row[c];
+        de[i] = R(t.a);
+        qe[i] = R(t.b);
+      };
+      get(ls.mid[r2b][0], 0);
+      get(ls.mid[r2b][1] - 1, 1);
+      get(ls.mid[r2b][2] + 1, 3);
+      get(bot ? ls.dn[r2b][0] : ls.up[r3c][0], 2);
+      get(bot ? ls.dn[r2b][1] : ls.up[r3c][1] - 1, 5);
+      get(bot ? ls.dn[r2b][2] : ls.up[r3c][2] + 1, 6);
+      get(top ? ls.up[r3b][0] : ls.dn[r2][0], 4);
+      get(top ? ls.up[r3b][1] : ls.dn[r2][1] + 1, 7);
+      get(top ? ls.up[r3b][2] : ls.dn[r2][2] - 1, 8);
+      n2 = rebuild(j - 1, f2, f1, v1.ph, s2, s1, v1.ps, de, qe);
+    }
+    if constexpr (STORE) {
+      const int y = j - 2;
+      const bool bot = at_bottom(y), top = at_top(y);
+      R g[8];
+      auto get = [&](const S *row, int k) { g[k] = R(row[c]); };
+      get(ls.hmid[r3c][0] - 1, 0);
+      get(ls.hmid[r3c][1] + 1, 2);
+      get(bot ? ls.hdn[r3c][0] : ls.hup[r4c][0], 1);
+      get(bot ? ls.hdn[r3c][1] : ls.hup[r4c][1] - 1, 4);
+      get(bot ? ls.hdn[r3c][2] : ls.hup[r4c][2] + 1, 5);
+      get(top ? ls.hup[r4b][0] : ls.hdn[r3b][0], 3);
+      get(top ? ls.hup[r4b][1] : ls.hdn[r3b][1] + 1, 6);
+      get(top ? ls.hup[r4b][2] : ls.hdn[r3b][2] - 1, 7);
+      if (bot) {
+        m2 = v2;
+        f3 = f2;
+      }
+      Scalars<R> nn = n2;
+      R fn = f1;
+      if (top) {
+        nn = v2;
+        fn = f2;
+      }
+      R ox, oy;
+      collide_row(y, m2, v2, nn, f3, f2, fn, s2, ux2, uy2, dd, qd, g, ox, oy);
+      bad |= interior && !isfinite(v2.ph + v2.ps + ox + oy);
+      const unsigned rcs = unsigned(y) * rows_s;
+#pragma unroll
+      for (int i = 0; i < 9; ++i)
+        PairIO<S>::template store<P::kStorePol>(S(dd[i]), S(qd[i]), rdst, cs_p,
+                                                rcs + unsigned(i) * nxb);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) bst<P>(g[i], rdst, cs_h, rcs + hb + unsigned(i) * nxh);
+      PairIO<A>::template store<P::kStorePol>(A(v2.ph), A(v2.ps), rdrest, brest_s,
+                                              unsigned(y) * rrow);
+      PairIO<A>::template store<P::kStorePol>(A(ox), A(oy), rauxo, baux_s, unsigned(y) * arow);
+    }
+
+    // slide the windows
+    if (second) {
+      m2 = v2;
+      v2 = n2;
+#pragma unroll
+      for (int i = 0; i < 9; ++i) {
+        dd[i] = de[i];
+        qd[i] = qe[i];
+      }
+    }
+    f3 = f2;
+    f2 = f1;
+    f1 = v1.ph;
+    s2 = s1;
+    s1 = v1.ps;
+    ux2 = ux1;
+    uy2 = uy1;
+    ux1 = ux;
+    uy1 = uy;
+    m1 = v1;
+    v1 = n1;
+#pragma unroll
+    for (int i = 0; i < 9; ++i) {
+      dc[i] = dk[i];
+      qc[i] = qk[i];
+    }
+    X0 = X1;
+    X1 = X2;
+    X2 = X3;
+    X3 = X4;
+    Y0 = Y1;
+    Y1 = Y2;
+    Y2 = Y3;
+    Y3 = Y4;
+    r3 = r3 == 2 ? 0 : r3 + 1;
+    r2 ^= 1;
+    r4 = (r4 + 1) & 3;
+  };
+
+  // The waits leave nothing of one loop in flight at the head of the next
+  // (see step_tile); the first four rows feed the second step only.
+  __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+  int j = j0;
+  for (int i = 0; i < 4; ++i, ++j) row(opaque_row(j), BoolC<false>{}, i >= 2);
+  __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+  for (int i = y0; i < y1; ++i, ++j) row(opaque_row(j), BoolC<true>{}, true);
+  if (bad) *a.flag = 1;
+}
+
+// One wavefront per tile.  XCD b % 8 walks the b-th band of rows, each strip
+// of it cut into tiles / nstrips chunks, one more in the first
+// tiles % nstrips strips, so that the band makes exactly `tiles` tiles.
+template <class P, bool GENR, bool HAS_S>
+__global__ void __launch_bounds__(kWave)
+lbm_pair_kernel(const PairArgs<P> pa) {
+  __shared__ PairLds<P> ls;
+  const StepArgs<P> &a = pa.s;
+  const int xcd = int(blockIdx.x % kXcds), tile = int(blockIdx.x / kXcds);
+  const int chunk = tile / a.nstrips, strip = tile - chunk * a.nstrips;
+  const int full = pa.tiles / a.nstrips;
+  const int chunks = full + (strip < pa.tiles - full * a.nstrips ? 1 : 0);
+  const Band b = band_of(xcd, a.ny, 1, 0, 1);
+  const int y0 = b.y0 + (b.y1 - b.y0) * chunk / chunks;
+  const int y1 = b.y0 + (b.y1 - b.y0) * (chunk + 1) / chunks;
+  if (y0 < y1) pair_tile<P, GENR, HAS_S>(a, pa.aux_out, strip, y0, y1, ls);
+}
+
 // ------------------------------------------------------------ batched step
 
 // A tile of the batched step: which simulation, which strip and row chunk.
@@ -2544,6 +2918,8 @@ struct lbm_handle {
   bool genr, has_s, ns;
   bool resident;  // step stores with the default cache policy (cache_resident)
   int waves_resident;  // step wavefronts the device holds at once (0: unknown)
+  int pair_plan;       // tiles per XCD of the two-step kernel (plan_pair_tiles)
+  int pair_tiles;      // the plan in use: 0 under a tile height set by the caller
   int block_plan;      // steps per launch of the block kernel (plan_block_steps)
   int block_steps;     // the plan in use: 0 under a tile height set by the caller
   std::string kernel;  // the step kernel variant, as a profiler names it
@@ -2647,6 +3023,8 @@ hipError_t launch_step_prec(lbm_handle *h, int *waves_per_cu) {
                   : launch_step<P, K, false, false, true>(h, waves_per_cu);
 }
 
+int pair_strips(const lbm_params &p) { return (p.nx + kPairCols - 1) / kPairCols; }
+
 // Blocks a launch of `steps` steps takes.
 int block_count(const lbm_params &p, int steps) {
   const int hx = p.precision == LBM_FP16DEV ? block_halo_x<F16>(steps) : block_halo_x<F32>(steps);
@@ -2674,6 +3052,33 @@ hipError_t launch_block_as(lbm_handle *h, const BlockLaunch &l, int *blocks_per_
                      dim3((b.ntiles + kXcds - 1) / kXcds * kXcds),
                      dim3(kBlockSide * kBlockSide), 0, h->stream, b);
   return hipGetLastError();
+}
+
+// A launch of the two-step kernel; with waves_per_cu set, instead the number
+// of its wavefronts one compute unit holds at once.
+template <class P, bool GENR, bool HAS_S>
+hipError_t launch_pair_as(lbm_handle *h, const BlockLaunch &l, int *waves_per_cu) {
+  if (waves_per_cu)
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(waves_per_cu,
+                                                        lbm_pair_kernel<P, GENR, HAS_S>, kWave, 0);
+  PairArgs<P> b;
+  b.s = step_args<P>(h, h->cur);
+  b.s.aux = static_cast<typename P::A *>(const_cast<void *>(l.aux_in));
+  b.s.nstrips = pair_strips(h->p);
+  b.aux_out = static_cast<typename P::A *>(l.aux_out);
+  b.tiles = h->pair_tiles;
+  hipLaunchKernelGGL((lbm_pair_kernel<P, GENR, HAS_S>), dim3(kXcds * b.tiles), dim3(kWave), 0,
+                     h->stream, b);
+  return hipGetLastError();
+}
+
+template <class P>
+hipError_t launch_pair(lbm_handle *h, const BlockLaunch &l, int *w) {
+  if (h->genr)
+    return h->has_s ? launch_pair_as<P, true, true>(h, l, w)
+                    : launch_pair_as<P, true, false>(h, l, w);
+  return h->has_s ? launch_pair_as<P, false, true>(h, l, w)
+                  : launch_pair_as<P, false, false>(h, l, w);
 }
 
 template <class P>
@@ -2826,6 +3231,34 @@ hipError_t run_block(lbm_handle *h, const BlockLaunch &l, int *blocks_per_cu = n
   }
 }
 
+// Two steps of h in one launch (or, with waves_per_cu set, the occupancy of
+// its two-step kernel).
+hipError_t run_pair(lbm_handle *h, const BlockLaunch &l, int *waves_per_cu = nullptr) {
+  if (h->p.precision == LBM_FP64)
+    return h->resident ? launch_pair<F64C>(h, l, waves_per_cu)
+                       : launch_pair<F64>(h, l, waves_per_cu);
+  return h->resident ? launch_pair<F32C>(h, l, waves_per_cu) : launch_pair<F32>(h, l, waves_per_cu);
+}
+
+// Tiles per XCD of the two-step kernel, 0 where lbm_step_kernel is used:
+// float16 storage (its step is bound by vector issue, which two steps per
+// launch do not lower), a prescribed velocity, and grids whose tiles would be
+// so low that the four rows a tile walks beyond its own outweigh the gain.
+// All wavefront slots take one tile (slots: per XCD), or as many as keep the
+// tiles at 40 rows or fewer.  us per step, lbm_step_kernel -> this:
+// float32 600^2 (3.2 rows) 20.6 -> 20.9, 640^2 (3.75) 23.7 -> 21.2, 720^2
+// (4.6) 26.3 -> 24.0; float64 450^2 (3.9) 22.5 -> 23.4, 512^2 (5.0)
+// 27.0 -> 26.1.  4096^2 float32 with tiles of 148, 74, 37 rows: 523, 497,
+// 485; 2048^2 with 37 and 18 rows: 134.0 and 134.2.
+int plan_pair_tiles(const lbm_params &p, int slots) {
+  if (slots <= 0 || p.precision == LBM_FP16DEV || p.flow != LBM_FLOW_NS) return 0;
+  if (p.ny < 16) return 0;  // the rows a tile reaches past the grid wrap once
+  const double rows = double(pair_strips(p)) * p.ny / kXcds / slots;  // mean tile height
+  if (rows < (p.precision == LBM_FP32 ? 3.7 : 4.7)) return 0;
+  const long long tiles = (long long)slots * (long long)std::ceil(rows / 40.0);
+  return int(std::max<long long>(tiles, pair_strips(p)));  // a chunk per strip at least
+}
+
 // Time steps per launch of the block kernel, 0 where lbm_step_kernel is
 // faster.  A launch whose blocks all run at once costs its fixed part plus
 // its steps, and a second round of blocks doubles it, so the most steps are
@@ -2944,6 +3377,19 @@ int query_block_steps(lbm_handle *h) {
     return 0;
   }
   return plan_block_steps(h, cus, cus * per_cu);
+}
+
+// Tiles per XCD of h's two-step kernel on the current device.
+int query_pair_tiles(lbm_handle *h) {
+  int dev = 0, cus = 0, per_cu = 0;
+  if (h->p.precision == LBM_FP16DEV || !h->ns) return 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+      run_pair(h, BlockLaunch{}, &per_cu) != hipSuccess) {
+    (void)hipGetLastError();
+    return 0;
+  }
+  return plan_pair_tiles(h->p, cus * per_cu / kXcds);
 }
 
 template <class P>
@@ -3092,6 +3538,7 @@ lbm_status lbm_create(const lbm_params *params, void *dev_ws, size_t ws_bytes,
   h->waves_resident = query_waves_resident(h);
   plan_tiles(h);
   h->block_plan = h->block_steps = query_block_steps(h);
+  h->pair_plan = h->pair_tiles = query_pair_tiles(h);
   h->kernel = kernel_name_of(h);
   int dev = -1;
   h->fixed_scratch = hipStreamGetDevice(h->stream, &dev) == hipSuccess ? fixed_scratch_of(dev)
@@ -3152,29 +3599,33 @@ lbm_status lbm_step(lbm_handle *h, int64_t nsteps) {
     return LBM_OK;
   };
   int64_t left = nsteps;
-  if (h->block_steps > 0 && left > 1) {
-    // The blocks of one launch overlap, so a launch cannot update the
-    // previous velocity in place: launches write it alternately to the
-    // scratch planes and back, an even number of them.
-    const bool flips = h->ns && h->p.precision != LBM_FP16DEV;
-    void *const aux[2] = {auxp(h), flips ? scratch(h) : auxp(h)};
-    int64_t launches = (left + h->block_steps - 1) / h->block_steps;
-    if (flips && launches % 2) {
-      if (launches < left) {
-        ++launches;
-      } else {  // one step per launch: the odd step goes below, in place
-        --launches;
-      }
-    }
-    int64_t steps = h->block_steps == 1 ? launches : left;
-    left -= steps;
+  // Launches of several steps read the previous velocity where others write
+  // it, so they cannot update it in place: they write it alternately to the
+  // scratch planes and back, an even number of them.
+  const bool flips = h->ns && h->p.precision != LBM_FP16DEV;
+  void *const aux[2] = {auxp(h), flips ? scratch(h) : auxp(h)};
+  auto alternate = [&](int64_t launches, int64_t steps, auto run) {
     for (int64_t i = 0; i < launches; ++i) {
       const int64_t rest = launches - i;
       const BlockLaunch l = {int((steps + rest - 1) / rest), aux[i % 2], aux[(i + 1) % 2]};
-      const lbm_status st = after(run_block(h, l), l.steps);
+      const lbm_status st = after(run(l), l.steps);
       if (st != LBM_OK) return st;
       steps -= l.steps;
+      left -= l.steps;
     }
+    return LBM_OK;
+  };
+  if (h->block_steps > 0 && left > 1) {
+    int64_t launches = (left + h->block_steps - 1) / h->block_steps;
+    if (flips && launches % 2) launches += launches < left ? 1 : -1;  // the rest goes in place
+    const lbm_status st = alternate(launches, h->block_steps == 1 ? launches : left,
+                                    [&](const BlockLaunch &l) { return run_block(h, l); });
+    if (st != LBM_OK) return st;
+  } else if (h->pair_tiles > 0) {
+    const int64_t launches = left / 4 * 2;
+    const lbm_status st = alternate(launches, 2 * launches,
+                                    [&](const BlockLaunch &l) { return run_pair(h, l); });
+    if (st != LBM_OK) return st;
   }
   for (; left > 0; --left) {
     const lbm_status st = after(run_step(h), 1);
@@ -3381,10 +3832,11 @@ lbm_status lbm_set_tile_rows(lbm_handle *h, int32_t rows) {
   if (rows == 0) {
     plan_tiles(h);
     h->block_steps = h->block_plan;
+    h->pair_tiles = h->pair_plan;
   } else {
     h->rows = rows;
     taper_of(h);
-    h->block_steps = 0;
+    h->block_steps = h->pair_tiles = 0;
   }
   return LBM_OK;
 }
