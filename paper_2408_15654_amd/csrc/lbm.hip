@@ -39,14 +39,17 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <limits>
 #include <map>
 #include <mutex>
 #include <new>
 #include <string>
+#include <thread>
 #include <utility>
 #include <vector>
 
@@ -2924,6 +2927,7 @@ struct lbm_handle {
   int block_steps;     // the plan in use: 0 under a tile height set by the caller
   std::string kernel;  // the step kernel variant, as a profiler names it
   std::string err;
+  int device;             // the stream's device, -1 if unknown
   double *fixed_scratch;  // this device's copy of the static read-back scratch
 };
 
@@ -3167,6 +3171,318 @@ lbm_status hip_check(lbm_handle *h, hipError_t e, const char *what) {
   return fail(h, LBM_EDEVICE, std::string(what) + ": " + hipGetErrorString(e));
 }
 
+
+// ---- host transfers.  Copies between the caller's pageable memory and the
+// device go through pinned staging in chunks: the device copies at the rate
+// of the link (57 GB/s pinned, against 18 GB/s read and 29 GB/s written for
+// pageable memory), and for large ones worker threads copy between staging
+// and the caller's memory meanwhile and take the page faults of memory the
+// caller has not touched yet, which cost one thread more than the link does
+// (128 MB: 2.4 ms on the link, 7-8 ms of first touches).  Only the calling
+// thread makes HIP calls: a new thread's first one takes about 3 ms.
+// Measured, direct -> this: the five fields of 64^2 0.16 -> 0.05 ms, 512^2
+// 0.67 -> 0.43, 1000^2 2.3 -> 1.2, 2048^2 (168 MB) 17 -> 5.1; initial fields of
+// 2048^2 7 -> 3.7 ms.
+
+constexpr size_t kChunkBytes = 2u << 20;  // a huge page of host memory
+constexpr int kSlots = 12;                // chunks in staging
+constexpr int kWorkers = 6;
+// Size of the largest piece from which threads help: the pages of smaller
+// arrays come singly, and six threads that fault them in at once take longer
+// than one (the fields of 512^2, 2 MB each: 3.9 ms against 0.6).
+constexpr size_t kThreadedBytes = 4u << 20;
+
+struct Staging {
+  char *mem = nullptr;  // the sticky flag's copy, then the chunks
+  size_t bytes = 0;
+  hipEvent_t done[kSlots] = {};
+};
+constexpr size_t kStagingHead = 256;
+
+// Idle staging buffers: at most kIdle of them (24 MiB each at most), freed
+// when the last handle is destroyed.
+class StagingPool {
+ public:
+  void enter() {
+    std::lock_guard<std::mutex> lock(mu_);
+    ++handles_;
+  }
+  void leave() {
+    Staging all[kIdle];
+    int n = 0;
+    {
+      std::lock_guard<std::mutex> lock(mu_);
+      if (--handles_ == 0)
+        while (count_ > 0) all[n++] = idle_[--count_];
+    }
+    while (n > 0) release(all[--n]);
+  }
+  // A buffer of at least `bytes` (false: none to be had).
+  bool take(size_t bytes, Staging *out) {
+    {
+      std::lock_guard<std::mutex> lock(mu_);
+      for (int i = 0; i < count_; ++i)
+        if (idle_[i].bytes >= bytes) {
+          *out = idle_[i];
+          idle_[i] = idle_[--count_];
+          return true;
+        }
+    }
+    Staging s;
+    s.bytes = size_t(1) << 18;
+    while (s.bytes < bytes) s.bytes *= 2;
+    s.bytes = std::min(s.bytes, kStagingHead + kSlots * kChunkBytes);
+    bool ok = hipHostMalloc(reinterpret_cast<void **>(&s.mem), s.bytes, hipHostMallocPortable) ==
+              hipSuccess;
+    if (!ok) s.mem = nullptr;
+    for (int w = 0; w < kSlots && ok; ++w)
+      ok = hipEventCreateWithFlags(&s.done[w], hipEventDisableTiming) == hipSuccess;
+    if (!ok) {
+      release(s);
+      (void)hipGetLastError();
+      return false;
+    }
+    *out = s;
+    return true;
+  }
+  void give(Staging s) {
+    {
+      std::lock_guard<std::mutex> lock(mu_);
+      if (count_ < kIdle) {
+        idle_[count_++] = s;
+        return;
+      }
+      for (Staging &o : idle_)  // keep the larger ones
+        if (o.bytes < s.bytes) std::swap(o, s);
+    }
+    release(s);
+  }
+
+ private:
+  static constexpr int kIdle = 2;
+  static void release(Staging &s) {
+    for (hipEvent_t e : s.done)
+      if (e) (void)hipEventDestroy(e);
+    if (s.mem) (void)hipHostFree(s.mem);
+  }
+  std::mutex mu_;
+  Staging idle_[kIdle];
+  int count_ = 0;
+  long long handles_ = 0;
+};
+StagingPool g_staging;
+
+// Device memory and the caller's, to be copied either way.
+struct Piece {
+  char *dev;
+  char *host;
+  size_t bytes;
+};
+
+struct NoCheck {
+  bool operator()(int, const char *, size_t) const { return true; }
+};
+
+// Copies the pieces on h's stream, to the device or from it, and waits for
+// them.  From the device: the sticky flag is read first (*flag), and nothing
+// reaches the caller's memory if it is set.  To the device: `check` sees all
+// of the host memory; if it refuses some, the copy ends (*refused).  planes:
+// the pieces are scratch planes one after another, whose gaps may be copied.
+template <class Check>
+hipError_t transfer(lbm_handle *h, const Piece *pieces, int npieces, bool planes, bool to_device,
+                    int *flag, bool *refused, Check check) {
+  if (npieces == 0) planes = false;
+  size_t total = 0;
+  for (int i = 0; i < npieces; ++i) total += pieces[i].bytes;
+  const size_t span = planes ? size_t(pieces[npieces - 1].dev + pieces[npieces - 1].bytes -
+                                      pieces[0].dev) : total;
+  // Small transfers are one chunk, scratch planes one device copy.  Larger
+  // ones are cut where the caller's memory passes from one huge page to the
+  // next: two workers that touch one page first would both clear it.
+  const bool single = span <= kChunkBytes;
+  auto first_part = [&](const Piece &p) {
+    return std::min(p.bytes, kChunkBytes - reinterpret_cast<uintptr_t>(p.host) % kChunkBytes);
+  };
+  auto parts_of = [&](const Piece &p) {
+    return 1 + (long long)((p.bytes - first_part(p) + kChunkBytes - 1) / kChunkBytes);
+  };
+  long long chunks = single ? 1 : 0;
+  for (int i = 0; i < npieces && !single; ++i) chunks += parts_of(pieces[i]);
+  const int slots = int(std::min<long long>(chunks, kSlots));
+  Staging st;
+  if (!g_staging.take(kStagingHead + (single ? span : slots * kChunkBytes), &st)) {
+    // no pinned memory: directly
+    hipError_t e = hipSuccess;
+    if (flag) {
+      e = hipMemcpyAsync(flag, flagp(h), sizeof(int), hipMemcpyDeviceToHost, h->stream);
+      if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
+      if (e != hipSuccess || *flag) return e;
+    }
+    for (int i = 0; i < npieces; ++i)
+      if (to_device && !check(i, pieces[i].host, pieces[i].bytes)) {
+        *refused = true;
+        return e;
+      }
+    for (int i = 0; i < npieces && e == hipSuccess; ++i)
+      e = to_device ? hipMemcpyAsync(pieces[i].dev, pieces[i].host, pieces[i].bytes,
+                                     hipMemcpyHostToDevice, h->stream)
+                    : hipMemcpyAsync(pieces[i].host, pieces[i].dev, pieces[i].bytes,
+                                     hipMemcpyDeviceToHost, h->stream);
+    const hipError_t last = hipStreamSynchronize(h->stream);
+    return e != hipSuccess ? e : last;
+  }
+  auto slot = [&](long long k) { return st.mem + kStagingHead + size_t(k % slots) * kChunkBytes; };
+  // f(piece, offset in it, bytes, offset in the slot) for the parts of chunk
+  // k, until one is false
+  auto each_part = [&](long long k, auto f) {
+    size_t at = 0;
+    for (int i = 0; i < npieces; ++i) {
+      const Piece &p = pieces[i];
+      if (single) {
+        if (planes) at = size_t(p.dev - pieces[0].dev);
+        if (!f(i, size_t(0), p.bytes, at)) return false;
+        at += p.bytes;
+        continue;
+      }
+      const long long n = parts_of(p);
+      if (k < n) {
+        const size_t off = k == 0 ? 0 : first_part(p) + size_t(k - 1) * kChunkBytes;
+        return f(i, off, k == 0 ? first_part(p) : std::min(kChunkBytes, p.bytes - off), size_t(0));
+      }
+      k -= n;
+    }
+    return true;
+  };
+  auto host_part = [&](long long k) {  // between the slot and the caller's memory
+    return each_part(k, [&](int i, size_t off, size_t n, size_t in_slot) {
+      char *const mem = pieces[i].host + off;
+      if (!to_device) {
+        std::memcpy(mem, slot(k) + in_slot, n);
+        return true;
+      }
+      if (!check(i, mem, n)) return false;
+      std::memcpy(slot(k) + in_slot, mem, n);
+      return true;
+    });
+  };
+  auto device_part = [&](long long k) {  // between the slot and the device
+    hipError_t e = hipSuccess;
+    if (single && planes)
+      return to_device ? hipMemcpyAsync(pieces[0].dev, slot(0), span, hipMemcpyHostToDevice,
+                                        h->stream)
+                       : hipMemcpyAsync(slot(0), pieces[0].dev, span, hipMemcpyDeviceToHost,
+                                        h->stream);
+    each_part(k, [&](int i, size_t off, size_t n, size_t in_slot) {
+      e = to_device ? hipMemcpyAsync(pieces[i].dev + off, slot(k) + in_slot, n,
+                                     hipMemcpyHostToDevice, h->stream)
+                    : hipMemcpyAsync(slot(k) + in_slot, pieces[i].dev + off, n,
+                                     hipMemcpyDeviceToHost, h->stream);
+      return e == hipSuccess;
+    });
+    return e != hipSuccess || single ? e : hipEventRecord(st.done[k % slots], h->stream);
+  };
+  auto device_done = [&](long long k) {
+    return single ? hipStreamSynchronize(h->stream) : hipEventSynchronize(st.done[k % slots]);
+  };
+  // The last chunk of each slot that the workers may take up, and that they
+  // have finished; worker w has chunks w, w + threads, ...
+  std::atomic<long long> open[kSlots], closed[kSlots];
+  for (int i = 0; i < kSlots; ++i) {
+    open[i] = to_device ? i : -1;  // every slot is empty at first
+    closed[i] = -1;
+  }
+  std::atomic<bool> stop{false}, bad{false};
+  size_t largest = 0;
+  for (int i = 0; i < npieces; ++i) largest = std::max(largest, pieces[i].bytes);
+  int threads = largest >= kThreadedBytes ? kWorkers : 0;
+  auto work = [&](int w) {
+    for (long long k = w; k < chunks; k += threads) {
+      while (open[k % slots] < k) {
+        if (stop) return;
+        std::this_thread::yield();
+      }
+      if (!host_part(k)) {
+        bad = stop = true;
+        return;
+      }
+      closed[k % slots] = k;
+    }
+  };
+  std::thread pool[kWorkers];
+  int started = 0;
+  for (; started < threads; ++started) {
+    try {
+      pool[started] = std::thread(work, started);
+    } catch (...) {  // no thread to be had
+      break;
+    }
+  }
+  if (started < threads) {  // some chunks would have no worker: none takes any
+    stop = true;
+    for (int w = 0; w < started; ++w) pool[w].join();
+    stop = false;
+    started = threads = 0;
+    for (int i = 0; i < kSlots; ++i) closed[i] = -1;
+  }
+  // chunk k has passed between its slot and the caller's memory
+  auto host_done = [&](long long k) {
+    if (threads == 0) return true;
+    while (closed[k % slots] < k && !stop) std::this_thread::yield();
+    return closed[k % slots] >= k;
+  };
+  hipError_t e = hipSuccess;
+  if (to_device) {
+    long long waited = 0;  // chunks the device has read
+    for (long long k = 0; k < chunks && e == hipSuccess && !stop; ++k) {
+      // half the slots stay with the workers
+      for (; waited <= k - std::max(1, slots / 2) && e == hipSuccess; ++waited) {
+        e = device_done(waited);
+        open[waited % slots] = waited + slots;
+      }
+      if (e != hipSuccess) break;
+      if (threads == 0 && !host_part(k)) {
+        bad = true;
+        break;
+      }
+      if (!host_done(k)) break;
+      e = device_part(k);
+    }
+  } else {
+    int *const flag_copy = reinterpret_cast<int *>(st.mem);
+    if (flag)
+      e = hipMemcpyAsync(flag_copy, flagp(h), sizeof(int), hipMemcpyDeviceToHost, h->stream);
+    long long next = 0;  // first chunk the device has not been asked for
+    for (long long k = 0; k < chunks && e == hipSuccess; ++k) {
+      for (; next < chunks && next < k + slots && e == hipSuccess; ++next) {
+        if (next >= slots && next > k && threads > 0 && closed[next % slots] < next - slots) break;
+        if (next >= slots && !host_done(next - slots)) break;
+        e = device_part(next);
+      }
+      if (e == hipSuccess) e = device_done(k);
+      if (e != hipSuccess) break;
+      if (flag && k == 0 && *static_cast<volatile int *>(flag_copy)) break;
+      if (threads == 0)
+        host_part(k);
+      else
+        open[k % slots] = k;
+    }
+    if (e == hipSuccess && chunks == 0) e = hipStreamSynchronize(h->stream);
+    if (flag) *flag = *static_cast<volatile int *>(flag_copy);
+    for (long long k = std::max(0LL, chunks - slots);
+         k < chunks && e == hipSuccess && !(flag && *flag); ++k)
+      host_done(k);
+  }
+  stop = true;
+  for (int w = 0; w < started; ++w) pool[w].join();
+  if (refused) *refused = bad;
+  // nothing of the staging may be in flight when it goes back
+  if (to_device || e != hipSuccess || (flag && *flag)) {
+    const hipError_t last = hipStreamSynchronize(h->stream);
+    if (e == hipSuccess) e = last;
+  }
+  g_staging.give(st);
+  return e;
+}
 
 template <class P>
 SiteArgs<P> site_args(lbm_handle *h) {
@@ -3487,19 +3803,20 @@ hipError_t launch_moments(lbm_handle *h, const double *sc, long long plane, doub
   return hipGetLastError();
 }
 
+// The three parts of the state after the step counter of a checkpoint.
+struct StatePieces {
+  Piece p[3];
+  StatePieces(lbm_handle *h, int cur, char *host) {
+    char *const pop = host + sizeof(int64_t), *const rst = pop + h->L.pop_bytes;
+    p[0] = Piece{static_cast<char *>(pops(h, cur)), pop, h->L.pop_bytes};
+    p[1] = Piece{static_cast<char *>(rest(h, cur)), rst, h->L.rest_bytes};
+    p[2] = Piece{static_cast<char *>(auxp(h)), rst + h->L.rest_bytes, h->L.aux_bytes};
+  }
+};
+
 lbm_status nonfinite(lbm_handle *h) {
   h->valid = false;
   return fail(h, LBM_ENONFINITE, "the device produced a non-finite value");
-}
-
-// Reads the sticky device flag (synchronising); marks the state invalid.
-lbm_status check_flag(lbm_handle *h) {
-  int flag = 0;
-  hipError_t e = hipMemcpyAsync(&flag, flagp(h), sizeof(int), hipMemcpyDeviceToHost,
-                                h->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
-  if (e != hipSuccess) return hip_check(h, e, "reading the non-finite flag");
-  return flag ? nonfinite(h) : LBM_OK;
 }
 
 }  // namespace
@@ -3540,10 +3857,11 @@ lbm_status lbm_create(const lbm_params *params, void *dev_ws, size_t ws_bytes,
   h->block_plan = h->block_steps = query_block_steps(h);
   h->pair_plan = h->pair_tiles = query_pair_tiles(h);
   h->kernel = kernel_name_of(h);
-  int dev = -1;
-  h->fixed_scratch = hipStreamGetDevice(h->stream, &dev) == hipSuccess ? fixed_scratch_of(dev)
-                                                                      : nullptr;
+  h->device = -1;
+  if (hipStreamGetDevice(h->stream, &h->device) != hipSuccess) h->device = -1;
+  h->fixed_scratch = fixed_scratch_of(h->device);
   (void)hipGetLastError();
+  g_staging.enter();
   *out = h;
   return LBM_OK;
 }
@@ -3552,27 +3870,36 @@ lbm_status lbm_init_fields(lbm_handle *h, const double *phi, const double *psi,
                            const double *ux, const double *uy) {
   if (!h) return LBM_EINVAL;
   if (!phi || !psi || !ux || !uy) return fail(h, LBM_EINVAL, "NULL field");
-  const long long n = (long long)h->p.nx * h->p.ny;
-  for (long long k = 0; k < n; ++k) {
-    if (!std::isfinite(phi[k]) || !std::isfinite(psi[k]) || !std::isfinite(ux[k]) ||
-        !std::isfinite(uy[k]))
-      return fail(h, LBM_EINVAL, "non-finite initial value");
-    if (h->p.eos == LBM_EOS_LANGMUIR && psi[k] >= 1.0)
-      return fail(h, LBM_EINVAL, "Langmuir EOS needs psi < 1");
-  }
+  const size_t n = size_t(h->p.nx) * size_t(h->p.ny);
   double *sc = scratch(h);
-  const long long pl = h->L.plane;
   const double *src[4] = {phi, psi, ux, uy};
-  for (int j = 0; j < 4; ++j) {
-    hipError_t e = hipMemcpyAsync(sc + j * pl, src[j], n * sizeof(double),
-                                  hipMemcpyHostToDevice, h->stream);
-    if (e != hipSuccess) return hip_check(h, e, "copying initial fields");
-  }
+  Piece pieces[4];
+  for (int j = 0; j < 4; ++j)
+    pieces[j] = Piece{reinterpret_cast<char *>(sc + j * h->L.plane),
+                      reinterpret_cast<char *>(const_cast<double *>(src[j])), n * sizeof(double)};
+  const bool langmuir = h->p.eos == LBM_EOS_LANGMUIR;
+  std::atomic<int> why{0};
+  bool refused = false;
+  hipError_t e = transfer(h, pieces, 4, true, true, nullptr, &refused,
+                          [&](int piece, const char *at, size_t bytes) {
+    const double *const v = reinterpret_cast<const double *>(at);
+    const size_t m = bytes / sizeof(double);
+    // |x| <= max rejects infinities and NaN alike; no branch per value
+    int bad = 0, big = 0;
+    for (size_t k = 0; k < m; ++k) bad |= !(std::fabs(v[k]) <= std::numeric_limits<double>::max());
+    if (langmuir && piece == 1)
+      for (size_t k = 0; k < m; ++k) big |= v[k] >= 1.0;
+    if (bad | big) why |= bad ? 1 : 2;
+    return !(bad | big);
+  });
+  if (e == hipSuccess && refused)
+    return fail(h, LBM_EINVAL, why & 1 ? "non-finite initial value" : "Langmuir EOS needs psi < 1");
+  if (e != hipSuccess) return hip_check(h, e, "copying initial fields");
   // from here on the stored state is being replaced: a failure leaves no
   // valid state (LBM_ESTATE until a later init or set_state succeeds)
   h->valid = false;
   h->cur = 0;
-  hipError_t e = run_init(h);
+  e = run_init(h);
   if (e == hipSuccess) e = hipMemsetAsync(flagp(h), 0, sizeof(int), h->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
   if (e != hipSuccess) return hip_check(h, e, "initialising");
@@ -3638,20 +3965,20 @@ lbm_status lbm_read_fields(lbm_handle *h, double *phi, double *psi, double *ux,
                            double *uy, double *P) {
   if (!h) return LBM_EINVAL;
   if (!h->valid) return fail(h, LBM_ESTATE, "no valid state");
-  lbm_status st = check_flag(h);
-  if (st != LBM_OK) return st;
   hipError_t e = run_macros(h);
   if (e != hipSuccess) return hip_check(h, e, "launching read-back kernels");
-  const long long n = (long long)h->p.nx * h->p.ny;
   double *dst[5] = {phi, psi, ux, uy, P};
-  for (int j = 0; j < 5; ++j) {
-    if (!dst[j]) continue;
-    e = hipMemcpyAsync(dst[j], scratch(h) + j * h->L.plane, n * sizeof(double),
-                       hipMemcpyDeviceToHost, h->stream);
-    if (e != hipSuccess) return hip_check(h, e, "copying fields");
-  }
-  e = hipStreamSynchronize(h->stream);
-  return hip_check(h, e, "reading fields");
+  Piece pieces[5];
+  int n = 0;
+  for (int j = 0; j < 5; ++j)
+    if (dst[j])
+      pieces[n++] = Piece{reinterpret_cast<char *>(scratch(h) + j * h->L.plane),
+                          reinterpret_cast<char *>(dst[j]),
+                          size_t(h->p.nx) * size_t(h->p.ny) * sizeof(double)};
+  int flag = 0;
+  e = transfer(h, pieces, n, true, false, &flag, nullptr, NoCheck{});
+  if (e != hipSuccess) return hip_check(h, e, "reading fields");
+  return flag ? nonfinite(h) : LBM_OK;
 }
 
 lbm_status lbm_moments(lbm_handle *h, lbm_moments_t *out) {
@@ -3772,40 +4099,27 @@ lbm_status lbm_get_state(lbm_handle *h, void *host_buf, size_t bytes) {
   if (!h) return LBM_EINVAL;
   if (!host_buf || bytes != lbm_state_bytes(h)) return fail(h, LBM_EINVAL, "bad buffer");
   if (!h->valid) return fail(h, LBM_ESTATE, "no valid state");
-  lbm_status st = check_flag(h);
-  if (st != LBM_OK) return st;
-  char *b = static_cast<char *>(host_buf);
-  std::memcpy(b, &h->step, sizeof(int64_t));
-  b += sizeof(int64_t);
-  const void *parts[3] = {pops(h, h->cur), rest(h, h->cur), auxp(h)};
-  const size_t sizes[3] = {h->L.pop_bytes, h->L.rest_bytes, h->L.aux_bytes};
-  hipError_t e = hipSuccess;
-  for (int j = 0; j < 3 && e == hipSuccess; ++j) {
-    e = hipMemcpyAsync(b, parts[j], sizes[j], hipMemcpyDeviceToHost, h->stream);
-    b += sizes[j];
-  }
-  if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
-  return hip_check(h, e, "saving state");
+  int flag = 0;
+  const StatePieces parts(h, h->cur, static_cast<char *>(host_buf));
+  const hipError_t e = transfer(h, parts.p, 3, false, false, &flag, nullptr, NoCheck{});
+  if (e != hipSuccess) return hip_check(h, e, "saving state");
+  if (flag) return nonfinite(h);
+  std::memcpy(host_buf, &h->step, sizeof(int64_t));
+  return LBM_OK;
 }
 
 lbm_status lbm_set_state(lbm_handle *h, const void *host_buf, size_t bytes) {
   if (!h) return LBM_EINVAL;
   if (!host_buf || bytes != lbm_state_bytes(h)) return fail(h, LBM_EINVAL, "bad buffer");
-  const char *b = static_cast<const char *>(host_buf);
   int64_t step;
-  std::memcpy(&step, b, sizeof(int64_t));
-  b += sizeof(int64_t);
+  std::memcpy(&step, host_buf, sizeof(int64_t));
   // the stored state is overwritten from here on: a failure leaves no valid
   // state (LBM_ESTATE until a later init or set_state succeeds)
   h->valid = false;
   h->cur = 0;
-  void *parts[3] = {pops(h, 0), rest(h, 0), auxp(h)};
-  const size_t sizes[3] = {h->L.pop_bytes, h->L.rest_bytes, h->L.aux_bytes};
-  hipError_t e = hipSuccess;
-  for (int j = 0; j < 3 && e == hipSuccess; ++j) {
-    e = hipMemcpyAsync(parts[j], b, sizes[j], hipMemcpyHostToDevice, h->stream);
-    b += sizes[j];
-  }
+  const StatePieces parts(h, 0, static_cast<char *>(const_cast<void *>(host_buf)));
+  bool refused = false;
+  hipError_t e = transfer(h, parts.p, 3, false, true, nullptr, &refused, NoCheck{});
   if (e == hipSuccess) e = hipMemsetAsync(flagp(h), 0, sizeof(int), h->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
   if (e != hipSuccess) return hip_check(h, e, "restoring state");
@@ -3820,6 +4134,7 @@ void lbm_destroy(lbm_handle *h) {
   // finish it before the caller can release or reuse that memory
   (void)hipStreamSynchronize(h->stream);
   delete h;
+  g_staging.leave();
 }
 
 const char *lbm_last_error(const lbm_handle *h) {
