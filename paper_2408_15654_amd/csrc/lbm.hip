@@ -4226,11 +4226,6 @@ struct lbm_batch {
   hipStream_t stream = nullptr;   // the caller's stream: all work goes here
   hipStream_t capture = nullptr;  // library stream used only to record graphs
   hipStream_t admit = nullptr;    // library stream for joiners' copies and init
-  // further streams used only to record graphs, and the events that tie them
-  // to the first (a process has four hardware queues)
-  static constexpr int kBranches = 4;
-  hipStream_t branch[kBranches] = {};
-  hipEvent_t fork[kBranches] = {};
   char *ws = nullptr;
   size_t ws_bytes = 0;
   int max_inst = 0;
@@ -4405,52 +4400,16 @@ lbm_status get_graph(lbm_batch *b, int K, hipGraphExec_t *out) {
     return LBM_OK;
   }
   if (b->graphs.size() >= 32) clear_graphs(b);
-  // The simulations of different variants do not touch each other, and one
-  // variant alone may not fill the device: each branch of the graph takes
-  // some of the variants through all K steps.  Largest variants first, each
-  // to the branch with the least work so far.  Measured, one after the other
-  // -> in branches: twelve served float32 solves (three variants of 21, 15
-  // and 11 us per step) 18.7 -> 13.9 ms, nine float16 ones 19.0 -> 12.8 ms;
-  // 180 steps of 32 channels (two variants, 80 and 27 us) 19.1 -> 17.6 ms.
-  int order[kClasses], present = 0;
-  for (int c = 0; c < kClasses; ++c)
-    if (b->class_n[c]) order[present++] = c;
-  std::sort(order, order + present, [&](int x, int y) { return b->class_n[x] > b->class_n[y]; });
-  const int branches = std::min(present, lbm_batch::kBranches);
-  int branch_of[kClasses] = {};
-  long long load[lbm_batch::kBranches] = {};
-  for (int i = 0; i < present; ++i) {
-    const int to = int(std::min_element(load, load + branches) - load);
-    branch_of[order[i]] = to;
-    load[to] += b->class_n[order[i]];
-  }
-  hipError_t e = hipSuccess;
-  for (int i = 1; i < branches && e == hipSuccess; ++i)
-    if (!b->branch[i]) e = hipStreamCreateWithFlags(&b->branch[i], hipStreamNonBlocking);
-  for (int i = 0; i < branches && branches > 1 && e == hipSuccess; ++i)
-    if (!b->fork[i]) e = hipEventCreateWithFlags(&b->fork[i], hipEventDisableTiming);
-  if (e != hipSuccess) return bhip(b, e, "creating the capture streams");
-  e = hipStreamBeginCapture(b->capture, hipStreamCaptureModeThreadLocal);
+  hipError_t e = hipStreamBeginCapture(b->capture, hipStreamCaptureModeThreadLocal);
   if (e != hipSuccess) return bhip(b, e, "beginning graph capture");
-  b->branch[0] = b->capture;
-  if (branches > 1) e = hipEventRecord(b->fork[0], b->capture);
-  for (int i = 1; i < branches && e == hipSuccess; ++i)
-    e = hipStreamWaitEvent(b->branch[i], b->fork[0], 0);
   for (int k = 0; k < K; ++k)
-    for (int i = 0; i < present; ++i) {
-      const int c = order[i];
-      launch_batch_class(c, class_blocks(b, c), b->branch[branch_of[c]],
-                         b->d_desc[class_precision(c)], b->d_tiles + b->class_off[c],
-                         b->d_count + c, k);
+    for (int c = 0; c < kClasses; ++c) {
+      if (!b->class_n[c]) continue;
+      launch_batch_class(c, class_blocks(b, c), b->capture, b->d_desc[class_precision(c)],
+                         b->d_tiles + b->class_off[c], b->d_count + c, k);
     }
-  for (int i = 1; i < branches && e == hipSuccess; ++i) {
-    e = hipEventRecord(b->fork[i], b->branch[i]);
-    if (e == hipSuccess) e = hipStreamWaitEvent(b->capture, b->fork[i], 0);
-  }
-  b->branch[0] = nullptr;
   hipGraph_t g = nullptr;
   hipError_t e2 = hipGetLastError();
-  if (e2 == hipSuccess) e2 = e;
   e = hipStreamEndCapture(b->capture, &g);
   if (e2 != hipSuccess) e = e2;
   hipGraphExec_t x = nullptr;
@@ -4756,10 +4715,6 @@ void lbm_batch_destroy(lbm_batch *b) {
     if (b->h_desc[p]) (void)hipHostFree(b->h_desc[p]);
   if (b->h_count) (void)hipHostFree(b->h_count);
   if (b->h_tiles) (void)hipHostFree(b->h_tiles);
-  for (hipStream_t st : b->branch)
-    if (st) (void)hipStreamDestroy(st);
-  for (hipEvent_t ev : b->fork)
-    if (ev) (void)hipEventDestroy(ev);
   if (b->capture) (void)hipStreamDestroy(b->capture);
   if (b->admit) (void)hipStreamDestroy(b->admit);
   delete b;
