@@ -4,8 +4,9 @@
 Workload: the 2048x2048 periodic many-drop field (400 drops, radii U[8,24],
 density and viscosity ratio 10, beta = 0.5, D = 0.01, M = 0.02, W = 4,
 random divergence-free initial velocity), float32 populations.  A step is one
-launch of the fused step kernel over the whole grid; inputs are resident in
-HBM before timing starts.  Prints ONE JSON line.
+time step of the whole grid; with float32 and float64 storage a launch of the
+fused kernel takes two of them.  Inputs are resident in HBM before timing
+starts.  Prints ONE JSON line.
 
     python bench.py [--gpus 1] [--steps K] [--warmup W] [--precision fp32]
                     [--no-cpu-baseline] [--copy-calibration]
@@ -41,6 +42,22 @@ def algorithmic_bytes_per_site(precision: str) -> int:
     from the previous phi, which the step reads anyway."""
     fields = 5 if precision == "fp16dev" else 4
     return 2 * 26 * STORE_BYTES[precision] + 2 * fields * FIELD_BYTES[precision]
+
+
+def field_kernel(step_kernel: str, precision: str, rows: int) -> tuple:
+    """The kernel that steps the 2048x2048 field, and its steps per launch:
+    with float64 and float32 storage lbm_step takes two steps per launch
+    there, unless the caller has set a tile height."""
+    if precision == "fp16dev" or rows:
+        return step_kernel, 1
+    storage, _columns, *rest = step_kernel[len("lbm_step_kernel<"):-1].split(", ")
+    return f"lbm_pair_kernel<{', '.join([storage] + rest[:2])}>", 2
+
+
+def launches_of(steps: int, steps_per_launch: int) -> int:
+    """Launches that `steps` steps take: the two-step kernel's come in even
+    numbers, and the steps left over are one launch each."""
+    return steps if steps_per_launch == 1 else steps - 2 * (steps // 4)
 
 
 def kernel_source_hash() -> str:
@@ -478,7 +495,12 @@ def main():
     sec = wall
     mlups = sites * args.steps / sec / 1e6
     bps = algorithmic_bytes_per_site(args.precision)
-    per_launch_ms = ms_events / args.steps
+    # A launch reads and writes the whole state once, whatever its steps: the
+    # roofline counts the bytes that the launches move, not those that one
+    # launch per step would.
+    kernel, steps_per_launch = field_kernel(sim.step_kernel_name(), args.precision, args.rows)
+    launches = launches_of(args.steps, steps_per_launch)
+    per_launch_ms = ms_events / launches
     achieved = bps * sites / (per_launch_ms * 1e-3) / 1e9
     traffic = measured_traffic(sites, args.precision)
 
@@ -498,11 +520,12 @@ def main():
         "config": {"workload": f"many_drops_2048x2048_{args.precision}", "nx": 2048,
                    "ny": 2048, "drops": 400, "density_ratio": 10, "viscosity_ratio": 10,
                    "precision": args.precision, "parallelism": "single GPU",
-                   "bytes_per_site_update": bps},
+                   "bytes_per_site_update": round(bps * launches / args.steps, 1)},
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
-                     "traffic": traffic, "kernel": sim.step_kernel_name(),
+                     "traffic": traffic, "kernel": kernel,
                      "kernel_ms_per_launch": round(per_launch_ms, 4),
+                     "steps_per_launch": round(args.steps / launches, 4),
                      # the counter bytes (reads past L2 and writes, halo
                      # re-reads included) over this run's launch time
                      "traffic_GBps": (round(traffic / (per_launch_ms * 1e-3) / 1e9, 1)

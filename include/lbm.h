@@ -160,8 +160,9 @@ lbm_status lbm_init_fields(lbm_handle *h, const double *phi, const double *psi,
  * stream-collide kernel (pull streaming with half-way bounce-back, the
  * gradient stencils, forces, closures (32a)-(32b), and the three MRT
  * collisions of Eqs. (21), (25), (29) in moment space).  On a grid too small
- * to fill the device a launch takes up to three steps (the same results);
- * it uses the read-back scratch of the workspace meanwhile.  Asynchronous.
+ * to fill the device a launch takes up to three steps, on a large one with
+ * float64 or float32 storage two steps (the same results); these launches
+ * use the read-back scratch of the workspace meanwhile.  Asynchronous.
  * Errors: LBM_EINVAL (nsteps < 0), LBM_ESTATE, LBM_EDEVICE. */
 lbm_status lbm_step(lbm_handle *h, int64_t nsteps);
 

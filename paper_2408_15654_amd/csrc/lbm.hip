@@ -25,7 +25,10 @@
 // (phi, psi, P, rho ux, rho uy) in float32, and the previous velocity is
 // rho u / rho(phi) of that record (aux holds only a prescribed velocity).
 //
-// One time step is ONE launch of lbm_step_kernel.  Each wavefront owns a
+// A time step is one launch of lbm_step_kernel, except where
+// lbm_block_kernel (grids too small to fill the device) or lbm_pair_kernel
+// (large float64 and float32 grids) take several steps in one launch with
+// the same results.  In lbm_step_kernel each wavefront owns a
 // strip of columns, 60 with one column per lane or 124 with two (float32
 // and float16 storage, even nx), plus two halo columns on each side, and
 // walks down a tile of rows.  For each row it pulls the f and g deviations
