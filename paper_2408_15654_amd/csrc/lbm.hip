@@ -3184,16 +3184,20 @@ lbm_status hip_check(lbm_handle *h, hipError_t e, const char *what) {
 // (128 MB: 2.4 ms on the link, 7-8 ms of first touches).  Only the calling
 // thread makes HIP calls: a new thread's first one takes about 3 ms.
 // Measured, direct -> this: the five fields of 64^2 0.16 -> 0.05 ms, 512^2
-// 0.67 -> 0.43, 1000^2 2.3 -> 1.2, 2048^2 (168 MB) 17 -> 5.1; initial fields of
-// 2048^2 7 -> 3.7 ms.
+// 0.64 -> 0.43, 1024^2 2.35 -> 1.6, 1448^2 4.7 -> 3.0, 2048^2 (168 MB) 17 ->
+// 4.8; initial fields of 1448^2 4.0 -> 3.2, of 2048^2 8 -> 3.7 ms.
 
 constexpr size_t kChunkBytes = 2u << 20;  // a huge page of host memory
 constexpr int kSlots = 12;                // chunks in staging
 constexpr int kWorkers = 6;
-// Size of the largest piece from which threads help: the pages of smaller
-// arrays come singly, and six threads that fault them in at once take longer
-// than one (the fields of 512^2, 2 MB each: 3.9 ms against 0.6).
-constexpr size_t kThreadedBytes = 4u << 20;
+// Size of the largest piece from which threads help.  malloc maps blocks of 32
+// MiB and more afresh, in huge pages where the caller asks for them; smaller
+// ones may come from its heap, whose pages come singly, and six threads that
+// fault those in at once take longer than one and hold up the caller (the
+// fields of 1023x769, 6 MB each, in new memory: 5-9 ms with threads, 2.8-4
+// without, 3.9-5.1 for direct copies; of 2048^2, 34 MB each, 5 ms with
+// threads, 17 direct).
+constexpr size_t kThreadedBytes = 32u << 20;
 
 struct Staging {
   char *mem = nullptr;  // the sticky flag's copy, then the chunks

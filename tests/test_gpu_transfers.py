@@ -1,6 +1,6 @@
 """Host transfers (initial fields, fields, checkpoints) at the sizes where
 their path changes: one staging chunk (2 MiB in all), several chunks, and
-arrays large enough for worker threads (4 MiB); odd sizes, so that chunks end
+arrays large enough for worker threads (32 MiB); odd sizes, so that chunks end
 inside elements' neighbours and scratch planes have gaps."""
 import numpy as np
 import pytest
@@ -56,7 +56,19 @@ def test_fields_and_checkpoint_come_back(nx, ny, precision):
     other.close()
 
 
-@pytest.mark.parametrize("nx,ny", SIZES)
+def test_threaded_fields_come_back():
+    """Arrays of 34 MB: a prescribed velocity is kept as it is given, so with
+    float64 storage it reads back bit for bit."""
+    nx, ny = 2111, 2003
+    p, fields = problem(nx, ny, "fp64", flow="prescribed")
+    sim = lbm.Simulation(p)
+    sim.init_fields(*fields)
+    got = sim.read_fields()
+    assert np.array_equal(got["ux"], fields[2]) and np.array_equal(got["uy"], fields[3])
+    sim.close()
+
+
+@pytest.mark.parametrize("nx,ny", SIZES + [(2111, 2003)])
 def test_invalid_initial_values_are_found_anywhere(nx, ny):
     """A NaN, an infinity, or psi >= 1 under the Langmuir law, at the first
     and the last site of an array: refused, and the state before it stays."""
