@@ -3632,13 +3632,27 @@ int single_rows(const lbm_handle *h) {
 // with 15 rows of 1-row chunks per band, float64 365.8 -> 363.1 us with 3,
 // float16 storage unchanged; 512x512 float32, 16 rows of 64 in short
 // chunks: 15.8 us, 18.8 without, 17.2 with 48.
+// Where the band's tiles all run at once, the short chunks must not make a
+// second round: a chunk that waits for a slot costs a whole walk.  Only as
+// many rows are cut short as still fit.  us per step, a quarter of the band in
+// short chunks -> those that fit: float64 330^2 17.9 -> 13.9 (none fits), 370^2
+// 20.9 -> 18.4, 410^2 22.5 -> 19.8, 450^2 23.5 -> 22.8; float16 640^2 28.6 ->
+// 23.7, 704^2 34.3 -> 31.1, 768^2 35.5 -> 31.5, 1024x512 35.0 -> 31.1, 896^2
+// 42.6 -> 40.3, 960^2 44.1 -> 43.2; float32 630^2 23.9 -> 22.0, 571^2 18.1 ->
+// 16.9.  Not for float32 tiles of 3 rows, three wavefronts to a SIMD: 619^2
+// 20.5 -> 19.4, but 635^2 21.0 -> 21.9, 605x660 20.8 -> 22.1.
 void taper_of(lbm_handle *h) {
   h->tail_h = 1;
   h->tail_rows = 0;
   if (h->rows <= h->tail_h || h->waves_resident <= 0) return;
-  const long long strips = strips_of(h->p);
-  const long long round = h->waves_resident / (kXcds * strips) * h->tail_h;
-  h->tail_rows = int(std::min<long long>(round, h->p.ny / kXcds / 4));
+  const long long round = h->waves_resident / (kXcds * strips_of(h->p));  // chunks
+  h->tail_rows = int(std::min<long long>(round * h->tail_h, h->p.ny / kXcds / 4));
+  const int band = (h->p.ny + kXcds - 1) / kXcds;
+  auto chunks = [&] {
+    return (band - h->tail_rows + h->rows - 1) / h->rows + h->tail_rows / h->tail_h;
+  };
+  if ((band + h->rows - 1) / h->rows <= round && !(h->p.precision == LBM_FP32 && h->rows > 2))
+    while (h->tail_rows > 0 && chunks() > round) --h->tail_rows;
 }
 
 // Tile plan of a single-grid step: the tile height (single_rows) and the
