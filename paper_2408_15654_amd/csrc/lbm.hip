@@ -40,6 +40,7 @@
 // current row only, and every population is written once.  Workgroups walk
 // the tiles in one contiguous band per XCD.
 #include <hip/hip_runtime.h>
+#include <sys/mman.h>
 
 #include <algorithm>
 #include <atomic>
@@ -3199,6 +3200,17 @@ constexpr int kWorkers = 6;
 // threads, 17 direct).
 constexpr size_t kThreadedBytes = 32u << 20;
 
+// Asks for the whole pages of [mem, mem + n), which is about to be written, in
+// one call: new pages taken one fault at a time cost 0.45 us each.  Does
+// nothing where the kernel does not know the request.
+inline void want_pages(char *mem, size_t n) {
+  constexpr uintptr_t kPage = 4096;
+  constexpr int kPopulateWrite = 23;  // MADV_POPULATE_WRITE
+  const uintptr_t from = (reinterpret_cast<uintptr_t>(mem) + kPage - 1) / kPage * kPage;
+  const uintptr_t to = (reinterpret_cast<uintptr_t>(mem) + n) / kPage * kPage;
+  if (to >= from + 16 * kPage) (void)madvise(reinterpret_cast<void *>(from), to - from, kPopulateWrite);
+}
+
 struct Staging {
   char *mem = nullptr;  // the sticky flag's copy, then the chunks
   size_t bytes = 0;
@@ -3360,10 +3372,14 @@ hipError_t transfer(lbm_handle *h, const Piece *pieces, int npieces, bool planes
     }
     return true;
   };
+  size_t largest = 0;
+  for (int i = 0; i < npieces; ++i) largest = std::max(largest, pieces[i].bytes);
+  int threads = largest >= kThreadedBytes ? kWorkers : 0;
   auto host_part = [&](long long k) {  // between the slot and the caller's memory
     return each_part(k, [&](int i, size_t off, size_t n, size_t in_slot) {
       char *const mem = pieces[i].host + off;
       if (!to_device) {
+        if (threads == 0) want_pages(mem, n);
         std::memcpy(mem, slot(k) + in_slot, n);
         return true;
       }
@@ -3399,9 +3415,6 @@ hipError_t transfer(lbm_handle *h, const Piece *pieces, int npieces, bool planes
     closed[i] = -1;
   }
   std::atomic<bool> stop{false}, bad{false};
-  size_t largest = 0;
-  for (int i = 0; i < npieces; ++i) largest = std::max(largest, pieces[i].bytes);
-  int threads = largest >= kThreadedBytes ? kWorkers : 0;
   auto work = [&](int w) {
     for (long long k = w; k < chunks; k += threads) {
       while (open[k % slots] < k) {
