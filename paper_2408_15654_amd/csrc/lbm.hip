@@ -1989,6 +1989,12 @@ lbm_block_kernel(const BlockArgs<P> ba) {
 // up are pulled last and kept longest; one that a wall sends back is pulled
 // from its own row instead.  Columns are offset by 1, so that the shifted
 // reads of the edge lanes stay inside a row (their values are not used).
+//
+// Lanes read columns that other lanes wrote, so a row's writes must stay
+// before the reads that follow them, and those before the next row's writes.
+// The hardware runs a wavefront's LDS operations in order; lds_in_order()
+// between them holds the compiler to it (for one lane the addresses differ,
+// so nothing else does).
 template <class P>
 struct PairLds {
   using S = typename P::S;
@@ -2003,6 +2009,14 @@ struct PairLds {
 
 constexpr int kPairHalo = 4;                       // columns on each side
 constexpr int kPairCols = kWave - 2 * kPairHalo;   // columns stored
+
+// Orders the wavefront's LDS operations before this point before those after
+// it, for the compiler alone: no instruction.
+__device__ __forceinline__ void lds_in_order() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
 
 template <class P>
 struct PairArgs {
@@ -2178,6 +2192,7 @@ __device__ __forceinline__ void pair_tile(const StepArgs<P> &a, typename P::A *a
     collide_row(j, m1, v1, n1, X0, X1, X2, Y1, uxp, uyp, dc, qc, h, ux, uy);
     bad |= interior && j >= y0 && j < y1 && !isfinite(v1.ph + v1.ps + ux + uy);
     auto w = [&](int i) { return Two<S>{S(dc[i]), S(qc[i])}; };
+    lds_in_order();  // after the last row's reads
     ls.up[r3][0][c] = w(2);
     ls.up[r3][1][c] = w(5);
     ls.up[r3][2][c] = w(6);
@@ -2195,6 +2210,7 @@ __device__ __forceinline__ void pair_tile(const StepArgs<P> &a, typename P::A *a
     ls.hdn[r3][0][c] = S(h[3]);
     ls.hdn[r3][1][c] = S(h[6]);
     ls.hdn[r3][2][c] = S(h[7]);
+    lds_in_order();  // before this row's reads
 
     Scalars<R> n2 = {R(0), R(0), R(0)};
     R de[9], qe[9];
