@@ -60,6 +60,7 @@
 #include "lbm.h"
 #include "lbm_device.h"
 #include "arena.h"
+#include "tiling.h"
 
 using namespace lbm;
 
@@ -1496,32 +1497,6 @@ __device__ __forceinline__ void step_tile(const StepArgs<P> &a, const int strip,
   if (bad) *a.flag = 1;
 }
 
-// Workgroups of a launch per XCD: the hardware deals workgroups out to the
-// eight XCDs round-robin (workgroup b runs on XCD b % 8).
-constexpr int kXcds = 8;
-
-// The rows one XCD walks in a single-grid step, cut into chunks: `rows`
-// high (the last one possibly lower) up to the band's last tail_rows rows,
-// then short chunks (tail_h high, the last one possibly lower) over those.
-// Band x holds rows [x ny / 8, (x + 1) ny / 8).
-struct Band {
-  int y0, y1;    // the band's rows
-  int ys;        // first row of the short chunks
-  int nlong;     // chunks of at most `rows` rows in [y0, ys)
-  int nchunks;   // long and short
-};
-
-__host__ __device__ inline Band band_of(int x, int ny, int rows, int tail_rows, int tail_h) {
-  Band b;
-  b.y0 = int((long long)x * ny / kXcds);
-  b.y1 = int((long long)(x + 1) * ny / kXcds);
-  const int t = min(tail_rows, b.y1 - b.y0);
-  b.ys = b.y1 - t;
-  b.nlong = (b.ys - b.y0 + rows - 1) / rows;
-  b.nchunks = b.nlong + (t + tail_h - 1) / tail_h;
-  return b;
-}
-
 // Grid size of the single-grid step kernel: rounds of kXcds workgroups,
 // enough for the band with the most tiles.
 template <class P>
@@ -2007,8 +1982,7 @@ struct PairLds {
   S hdn[3][3][W];       // h_4, 7, 8 of rows j-2 .. j
 };
 
-constexpr int kPairHalo = 4;                       // columns on each side
-constexpr int kPairCols = kWave - 2 * kPairHalo;   // columns stored
+static_assert(kPairCols == kWave - 2 * kPairHalo, "a wavefront's columns");
 
 // Orders the wavefront's LDS operations before this point before those after
 // it, for the compiler alone: no instruction.
@@ -2319,22 +2293,15 @@ __device__ __forceinline__ void pair_tile(const StepArgs<P> &a, typename P::A *a
   if (bad) *a.flag = 1;
 }
 
-// One wavefront per tile.  XCD b % 8 walks the b-th band of rows, each strip
-// of it cut into tiles / nstrips chunks, one more in the first
-// tiles % nstrips strips, so that the band makes exactly `tiles` tiles.
+// One wavefront per tile (pair_tile_of).
 template <class P, bool GENR, bool HAS_S>
 __global__ void __launch_bounds__(kWave)
 lbm_pair_kernel(const PairArgs<P> pa) {
   __shared__ PairLds<P> ls;
   const StepArgs<P> &a = pa.s;
-  const int xcd = int(blockIdx.x % kXcds), tile = int(blockIdx.x / kXcds);
-  const int chunk = tile / a.nstrips, strip = tile - chunk * a.nstrips;
-  const int full = pa.tiles / a.nstrips;
-  const int chunks = full + (strip < pa.tiles - full * a.nstrips ? 1 : 0);
-  const Band b = band_of(xcd, a.ny, 1, 0, 1);
-  const int y0 = b.y0 + (b.y1 - b.y0) * chunk / chunks;
-  const int y1 = b.y0 + (b.y1 - b.y0) * (chunk + 1) / chunks;
-  if (y0 < y1) pair_tile<P, GENR, HAS_S>(a, pa.aux_out, strip, y0, y1, ls);
+  const PairTile t = pair_tile_of(int(blockIdx.x % kXcds), int(blockIdx.x / kXcds), a.ny, pa.tiles,
+                                  a.nstrips);
+  if (t.y0 < t.y1) pair_tile<P, GENR, HAS_S>(a, pa.aux_out, t.strip, t.y0, t.y1, ls);
 }
 
 // ------------------------------------------------------------ batched step
@@ -2941,7 +2908,7 @@ struct lbm_handle {
   bool genr, has_s, ns;
   bool resident;  // step stores with the default cache policy (cache_resident)
   int waves_resident;  // step wavefronts the device holds at once (0: unknown)
-  int pair_plan;       // tiles per XCD of the two-step kernel (plan_pair_tiles)
+  int pair_plan;       // tiles per XCD of the two-step kernel (pair_tiles_of)
   int pair_tiles;      // the plan in use: 0 under a tile height set by the caller
   int block_plan;      // steps per launch of the block kernel (plan_block_steps)
   int block_steps;     // the plan in use: 0 under a tile height set by the caller
@@ -3047,8 +3014,6 @@ hipError_t launch_step_prec(lbm_handle *h, int *waves_per_cu) {
                   : launch_step<P, K, false, false, true>(h, waves_per_cu);
 }
 
-int pair_strips(const lbm_params &p) { return (p.nx + kPairCols - 1) / kPairCols; }
-
 // Blocks a launch of `steps` steps takes.
 int block_count(const lbm_params &p, int steps) {
   const int hx = p.precision == LBM_FP16DEV ? block_halo_x<F16>(steps) : block_halo_x<F32>(steps);
@@ -3088,7 +3053,7 @@ hipError_t launch_pair_as(lbm_handle *h, const BlockLaunch &l, int *waves_per_cu
   PairArgs<P> b;
   b.s = step_args<P>(h, h->cur);
   b.s.aux = static_cast<typename P::A *>(const_cast<void *>(l.aux_in));
-  b.s.nstrips = pair_strips(h->p);
+  b.s.nstrips = pair_strips(h->p.nx);
   b.aux_out = static_cast<typename P::A *>(l.aux_out);
   b.tiles = h->pair_tiles;
   hipLaunchKernelGGL((lbm_pair_kernel<P, GENR, HAS_S>), dim3(kXcds * b.tiles), dim3(kWave), 0,
@@ -3592,25 +3557,6 @@ hipError_t run_pair(lbm_handle *h, const BlockLaunch &l, int *waves_per_cu = nul
   return h->resident ? launch_pair<F32C>(h, l, waves_per_cu) : launch_pair<F32>(h, l, waves_per_cu);
 }
 
-// Tiles per XCD of the two-step kernel, 0 where lbm_step_kernel is used:
-// float16 storage (its step is bound by vector issue, which two steps per
-// launch do not lower), a prescribed velocity, and grids whose tiles would be
-// so low that the four rows a tile walks beyond its own outweigh the gain.
-// All wavefront slots take one tile (slots: per XCD), or as many as keep the
-// tiles at 40 rows or fewer.  us per step, lbm_step_kernel -> this:
-// float32 600^2 (3.2 rows) 20.6 -> 20.9, 640^2 (3.75) 23.7 -> 21.2, 720^2
-// (4.6) 26.3 -> 24.0; float64 450^2 (3.9) 22.5 -> 23.4, 512^2 (5.0)
-// 27.0 -> 26.1.  4096^2 float32 with tiles of 148, 74, 37 rows: 523, 497,
-// 485; 2048^2 with 37 and 18 rows: 134.0 and 134.2.
-int plan_pair_tiles(const lbm_params &p, int slots) {
-  if (slots <= 0 || p.precision == LBM_FP16DEV || p.flow != LBM_FLOW_NS) return 0;
-  if (p.ny < 16) return 0;  // the rows a tile reaches past the grid wrap once
-  const double rows = double(pair_strips(p)) * p.ny / kXcds / slots;  // mean tile height
-  if (rows < (p.precision == LBM_FP32 ? 3.7 : 4.7)) return 0;
-  const long long tiles = (long long)slots * (long long)std::ceil(rows / 40.0);
-  return int(std::max<long long>(tiles, pair_strips(p)));  // a chunk per strip at least
-}
-
 // Time steps per launch of the block kernel, 0 where lbm_step_kernel is
 // faster.  A launch whose blocks all run at once costs its fixed part plus
 // its steps, and a second round of blocks doubles it, so the most steps are
@@ -3745,7 +3691,10 @@ int query_block_steps(lbm_handle *h) {
   return plan_block_steps(h, cus, cus * per_cu);
 }
 
-// Tiles per XCD of h's two-step kernel on the current device.
+// Tiles per XCD of h's two-step kernel on the current device, 0 where
+// lbm_step_kernel is used: where pair_tiles_of says so, for float16 storage
+// (its step is bound by vector issue, which two steps per launch do not
+// lower) and for a prescribed velocity.
 int query_pair_tiles(lbm_handle *h) {
   int dev = 0, cus = 0, per_cu = 0;
   if (h->p.precision == LBM_FP16DEV || !h->ns) return 0;
@@ -3755,7 +3704,7 @@ int query_pair_tiles(lbm_handle *h) {
     (void)hipGetLastError();
     return 0;
   }
-  return plan_pair_tiles(h->p, cus * per_cu / kXcds);
+  return pair_tiles_of(h->p.nx, h->p.ny, h->p.precision == LBM_FP32, cus * per_cu / kXcds);
 }
 
 template <class P>
