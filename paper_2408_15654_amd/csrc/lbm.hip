@@ -2914,7 +2914,6 @@ struct lbm_handle {
   int block_steps;     // the plan in use: 0 under a tile height set by the caller
   std::string kernel;  // the step kernel variant, as a profiler names it
   std::string err;
-  int device;             // the stream's device, -1 if unknown
   double *fixed_scratch;  // this device's copy of the static read-back scratch
 };
 
@@ -3192,9 +3191,30 @@ inline void want_pages(char *mem, size_t n) {
   if (to >= from + 16 * kPage) (void)madvise(reinterpret_cast<void *>(from), to - from, kPopulateWrite);
 }
 
+// Makes `dev` the calling thread's current device while it lives.
+class OnDevice {
+ public:
+  explicit OnDevice(int dev) {
+    ok_ = hipGetDevice(&before_) == hipSuccess &&
+          (before_ == dev || hipSetDevice(dev) == hipSuccess);
+    back_ = ok_ && before_ != dev;
+  }
+  ~OnDevice() {
+    if (back_) (void)hipSetDevice(before_);
+  }
+  OnDevice(const OnDevice &) = delete;
+  OnDevice &operator=(const OnDevice &) = delete;
+  bool ok() const { return ok_; }
+
+ private:
+  int before_ = 0;
+  bool ok_, back_;
+};
+
 struct Staging {
   char *mem = nullptr;  // the sticky flag's copy, then the chunks
   size_t bytes = 0;
+  int device = -1;      // of the events: streams of others refuse them
   hipEvent_t done[kSlots] = {};
 };
 constexpr size_t kStagingHead = 256;
@@ -3217,23 +3237,27 @@ class StagingPool {
     }
     while (n > 0) release(all[--n]);
   }
-  // A buffer of at least `bytes` (false: none to be had).
-  bool take(size_t bytes, Staging *out) {
+  // A buffer of at least `bytes` for a stream of `device` (false: none to be
+  // had).
+  bool take(size_t bytes, int device, Staging *out) {
     {
       std::lock_guard<std::mutex> lock(mu_);
       for (int i = 0; i < count_; ++i)
-        if (idle_[i].bytes >= bytes) {
+        if (idle_[i].bytes >= bytes && idle_[i].device == device) {
           *out = idle_[i];
           idle_[i] = idle_[--count_];
           return true;
         }
     }
+    const OnDevice on(device);
     Staging s;
+    s.device = device;
     s.bytes = size_t(1) << 18;
     while (s.bytes < bytes) s.bytes *= 2;
     s.bytes = std::min(s.bytes, kStagingHead + kSlots * kChunkBytes);
-    bool ok = hipHostMalloc(reinterpret_cast<void **>(&s.mem), s.bytes, hipHostMallocPortable) ==
-              hipSuccess;
+    bool ok = on.ok() &&
+              hipHostMalloc(reinterpret_cast<void **>(&s.mem), s.bytes, hipHostMallocPortable) ==
+                  hipSuccess;
     if (!ok) s.mem = nullptr;
     for (int w = 0; w < kSlots && ok; ++w)
       ok = hipEventCreateWithFlags(&s.done[w], hipEventDisableTiming) == hipSuccess;
@@ -3310,8 +3334,11 @@ hipError_t transfer(lbm_handle *h, const Piece *pieces, int npieces, bool planes
   for (int i = 0; i < npieces && !single; ++i) chunks += parts_of(pieces[i]);
   const int slots = int(std::min<long long>(chunks, kSlots));
   Staging st;
-  if (!g_staging.take(kStagingHead + (single ? span : slots * kChunkBytes), &st)) {
-    // no pinned memory: directly
+  int device = -1;
+  if (hipStreamGetDevice(h->stream, &device) != hipSuccess ||
+      !g_staging.take(kStagingHead + (single ? span : slots * kChunkBytes), device, &st)) {
+    // no staging: directly
+    (void)hipGetLastError();
     hipError_t e = hipSuccess;
     if (flag) {
       e = hipMemcpyAsync(flag, flagp(h), sizeof(int), hipMemcpyDeviceToHost, h->stream);
@@ -3856,9 +3883,9 @@ lbm_status lbm_create(const lbm_params *params, void *dev_ws, size_t ws_bytes,
   h->block_plan = h->block_steps = query_block_steps(h);
   h->pair_plan = h->pair_tiles = query_pair_tiles(h);
   h->kernel = kernel_name_of(h);
-  h->device = -1;
-  if (hipStreamGetDevice(h->stream, &h->device) != hipSuccess) h->device = -1;
-  h->fixed_scratch = fixed_scratch_of(h->device);
+  int dev = -1;
+  h->fixed_scratch = hipStreamGetDevice(h->stream, &dev) == hipSuccess ? fixed_scratch_of(dev)
+                                                                      : nullptr;
   (void)hipGetLastError();
   g_staging.enter();
   *out = h;

@@ -1,0 +1,101 @@
+// Checks of the library's host code over the stand-in runtime of
+// host_runtime.h.  `host_check NAME` runs one of them and prints "NAME ok".
+// Built and run by test_host_runtime.py.
+#include "host_runtime.h"
+
+#include <cmath>
+#include <functional>
+
+#include "lbm.h"
+
+#define CHECK(c)                                              \
+  do {                                                        \
+    if (!(c)) {                                               \
+      std::printf("line %d: %s\n", __LINE__, #c);             \
+      std::exit(1);                                           \
+    }                                                         \
+  } while (0)
+
+static lbm_params params(int nx, int ny, int precision) {
+  lbm_params p;
+  std::memset(&p, 0, sizeof p);
+  p.nx = nx, p.ny = ny, p.precision = precision;
+  p.phiA = 1, p.W = 4, p.M = 0.02, p.D = 0.01, p.r = 1;
+  p.rhoA = 10, p.rhoB = 1, p.muA = 1, p.muB = 0.1, p.sigma0 = 1e-3;
+  for (auto &row : p.s_free)
+    for (double &v : row) v = 1;
+  return p;
+}
+
+// A simulation on a stream of `device`, with the memory it needs.
+struct Sim {
+  lbm_params p;
+  std::vector<char> mem;
+  Stream stream;
+  lbm_handle *h = nullptr;
+  size_t n;
+  std::vector<double> field[5];
+  std::vector<char> state;
+
+  Sim(const lbm_params &q, int on = 0) : p(q), stream{on}, n(size_t(q.nx) * q.ny) {
+    const size_t bytes = lbm_workspace_bytes(&p);
+    CHECK(bytes > 0);
+    mem.resize(bytes + 256);
+    char *ws = mem.data() + (256 - reinterpret_cast<uintptr_t>(mem.data()) % 256) % 256;
+    CHECK(lbm_create(&p, ws, bytes, &stream, &h) == LBM_OK);
+    for (int j = 0; j < 5; ++j) {
+      field[j].resize(n);
+      for (size_t k = 0; k < n; ++k) field[j][k] = 0.5 + 1e-9 * double(k) * (j + 1);
+    }
+    state.resize(lbm_state_bytes(h));
+  }
+  ~Sim() { lbm_destroy(h); }
+  lbm_status init() {
+    return lbm_init_fields(h, field[0].data(), field[1].data(), field[2].data(), field[3].data());
+  }
+  lbm_status read() {
+    return lbm_read_fields(h, field[0].data(), field[1].data(), field[2].data(), field[3].data(),
+                           field[4].data());
+  }
+};
+
+static std::vector<char> batch_memory(lbm_batch **b, Stream *stream) {
+  std::vector<char> mem(size_t(64) << 20);
+  char *ws = mem.data() + (256 - reinterpret_cast<uintptr_t>(mem.data()) % 256) % 256;
+  CHECK(lbm_batch_create(8, ws, mem.size() - 256, stream, b) == LBM_OK);
+  return mem;
+}
+
+static int submit(lbm_batch *b, const lbm_params &p, int steps) {
+  const std::vector<double> f(size_t(p.nx) * p.ny, 0.25);
+  int32_t id = -1;
+  CHECK(lbm_batch_submit(b, &p, f.data(), f.data(), f.data(), f.data(), steps, &id) == LBM_OK);
+  return id;
+}
+
+// Transfers of every size work on a handle whose stream is not on the current
+// device, and after a handle of another device gave its staging back.
+static void other_device() {
+  for (const int side : {64, 512, 2100}) {
+    Sim one(params(side, side, LBM_FP32), 1), zero(params(side, side, LBM_FP32), 0);
+    for (Sim *s : {&one, &zero, &one}) {
+      CHECK(s->init() == LBM_OK);
+      CHECK(s->read() == LBM_OK);
+      CHECK(lbm_get_state(s->h, s->state.data(), s->state.size()) == LBM_OK);
+      CHECK(lbm_set_state(s->h, s->state.data(), s->state.size()) == LBM_OK);
+      CHECK(device == 0);
+    }
+  }
+  CHECK(pinned.empty() && events == 0);
+}
+
+int main(int argc, char **argv) {
+  const std::map<std::string, std::function<void()>> checks = {
+      {"other_device", other_device},
+  };
+  const auto it = argc > 1 ? checks.find(argv[1]) : checks.end();
+  if (it == checks.end()) return 2;
+  it->second();
+  std::printf("%s ok\n", argv[1]);
+  return 0;
+}
