@@ -4454,6 +4454,22 @@ lbm_status get_graph(lbm_batch *b, int K, const int *variants, int n, hipGraphEx
   return LBM_OK;
 }
 
+// The streams and events of the first `lanes` lanes, on the device of the
+// caller's stream, whatever device is current: its events are recorded there.
+hipError_t make_lanes(lbm_batch *b, int lanes) {
+  if (b->tie[lanes - 1]) return hipSuccess;
+  int dev = 0;
+  hipError_t e = hipStreamGetDevice(b->stream, &dev);
+  if (e != hipSuccess) return e;
+  const OnDevice on(dev);
+  if (!on.ok()) return hipErrorInvalidDevice;
+  for (int i = 1; i < lanes && e == hipSuccess; ++i)
+    if (!b->lane[i]) e = hipStreamCreateWithFlags(&b->lane[i], hipStreamNonBlocking);
+  for (int i = 0; i < lanes && e == hipSuccess; ++i)
+    if (!b->tie[i]) e = hipEventCreateWithFlags(&b->tie[i], hipEventDisableTiming);
+  return e;
+}
+
 // K steps of every variant present.  The simulations of different variants
 // do not touch each other, and one variant alone may not fill the device, so
 // they run side by side, each with a graph of its own: the largest first, each
@@ -4496,10 +4512,7 @@ lbm_status launch_chunk(lbm_batch *b, int K) {
     const lbm_status st = get_graph(b, K, order + i, lanes > 1 ? 1 : present, &graph[i]);
     if (st != LBM_OK) return st;
   }
-  for (int i = 1; i < lanes && e == hipSuccess; ++i)
-    if (!b->lane[i]) e = hipStreamCreateWithFlags(&b->lane[i], hipStreamNonBlocking);
-  for (int i = 0; i < lanes && lanes > 1 && e == hipSuccess; ++i)
-    if (!b->tie[i]) e = hipEventCreateWithFlags(&b->tie[i], hipEventDisableTiming);
+  if (lanes > 1) e = make_lanes(b, lanes);
   if (e != hipSuccess) return bhip(b, e, "creating the batch's streams");
   if (lanes > 1) e = hipEventRecord(b->tie[0], b->stream);
   for (int i = 1; i < lanes && e == hipSuccess; ++i)

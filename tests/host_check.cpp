@@ -76,7 +76,7 @@ static int submit(lbm_batch *b, const lbm_params &p, int steps) {
 // Transfers of every size work on a handle whose stream is not on the current
 // device, and after a handle of another device gave its staging back.
 static void other_device() {
-  for (const int side : {64, 512, 2100}) {
+  for (const int side : {64, 512, 700}) {
     Sim one(params(side, side, LBM_FP32), 1), zero(params(side, side, LBM_FP32), 0);
     for (Sim *s : {&one, &zero, &one}) {
       CHECK(s->init() == LBM_OK);
@@ -89,9 +89,34 @@ static void other_device() {
   CHECK(pinned.empty() && events == 0);
 }
 
+// A batch made on device 1 steps several kernel variants while device 0 is
+// current.
+static void other_device_batch() {
+  Stream stream{1};
+  lbm_batch *b = nullptr;
+  for (const int current : {0, 1}) {  // the device current at its creation
+    device = current;
+    const std::vector<char> mem = batch_memory(&b, &stream);
+    device = 0;
+    const int a = submit(b, params(40, 30, LBM_FP32), 50), c = submit(b, params(30, 20, LBM_FP64), 50);
+    CHECK(lbm_batch_step(b, 50) == LBM_OK);
+    std::vector<double> f(700 * 700);
+    CHECK(lbm_batch_read_fields(b, a, f.data(), nullptr, nullptr, nullptr, nullptr) == LBM_OK);
+    CHECK(lbm_batch_read_fields(b, c, f.data(), nullptr, nullptr, nullptr, nullptr) == LBM_OK);
+    CHECK(lbm_batch_retire(b, c) == LBM_OK);
+    const int d = submit(b, params(500, 150, LBM_FP32), 9);  // more than one staging chunk
+    CHECK(lbm_batch_step(b, 9) == LBM_OK);
+    CHECK(lbm_batch_read_fields(b, d, f.data(), f.data() + 75000, f.data() + 150000,
+                                f.data() + 225000, f.data() + 300000) == LBM_OK);
+    lbm_batch_destroy(b);
+    CHECK(pinned.empty() && events == 0 && streams == 0 && graphs == 0 && device == 0);
+  }
+}
+
 int main(int argc, char **argv) {
   const std::map<std::string, std::function<void()>> checks = {
       {"other_device", other_device},
+      {"other_device_batch", other_device_batch},
   };
   const auto it = argc > 1 ? checks.find(argv[1]) : checks.end();
   if (it == checks.end()) return 2;
