@@ -341,7 +341,10 @@ lbm_status lbm_batch_submit(lbm_batch *b, const lbm_params *params, const double
 
 /* Advance every admitted simulation by min(nsteps, its remaining steps);
  * asynchronous.  EINVAL: nsteps < 0.  A simulation whose state went
- * non-finite keeps stepping until a synchronising call on it reports it. */
+ * non-finite keeps stepping until a synchronising call on it reports it.
+ * EDEVICE: a launch failed.  Simulations some of whose launches had been
+ * enqueued by then have no valid state (LBM_ESTATE) and no steps left; the
+ * others are where the last whole chunk of launches left them. */
 lbm_status lbm_batch_step(lbm_batch *b, int64_t nsteps);
 
 /* Steps simulation id still has to run (0 = finished).  No device work. */

@@ -4518,18 +4518,29 @@ lbm_status launch_chunk(lbm_batch *b, int K) {
   for (int i = 1; i < lanes && e == hipSuccess; ++i)
     e = hipStreamWaitEvent(b->lane[i], b->tie[0], 0);
   long long load[lbm_batch::kLanes] = {};
+  bool started[kClasses] = {};  // on lanes: the variants whose steps are enqueued
   for (int i = 0; i < graphs && e == hipSuccess; ++i) {
     const int to = int(std::min_element(load, load + lanes) - load);
     load[to] += b->class_n[order[i]];
     e = hipGraphLaunch(graph[i], to ? b->lane[to] : b->stream);
+    started[order[i]] = lanes > 1 && e == hipSuccess;
   }
   // Also after an error: what was started has to end before the caller's
   // stream goes on.
   for (int i = 1; i < lanes; ++i) {
     hipError_t e2 = hipEventRecord(b->tie[i], b->lane[i]);
     if (e2 == hipSuccess) e2 = hipStreamWaitEvent(b->stream, b->tie[i], 0);
+    if (e2 != hipSuccess) (void)hipStreamSynchronize(b->lane[i]);
     if (e == hipSuccess) e = e2;
   }
+  // Of a chunk that failed, the started variants step on the device all the
+  // same: their simulations are no longer where they were, nor known to be a
+  // chunk further.
+  for (auto &in : b->inst)
+    if (e != hipSuccess && in.h && in.remaining > 0 && started[class_of(in.h)]) {
+      in.h->valid = false;
+      in.remaining = 0;
+    }
   return bhip(b, e, "launching the batch graphs");
 }
 

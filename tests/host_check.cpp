@@ -113,10 +113,43 @@ static void other_device_batch() {
   }
 }
 
+// A chunk of which a part fails: the simulations whose steps were started have
+// no valid state, the others keep theirs, and what was started is waited for.
+static void failed_chunk() {
+  std::vector<double> out(40 * 400);
+  auto readable = [&](lbm_batch *b, int id) {
+    return lbm_batch_read_fields(b, id, out.data(), nullptr, nullptr, nullptr, nullptr) == LBM_OK;
+  };
+  for (const int failing : {0, 1, 2}) {  // the largest variants start first
+    Stream stream{0};
+    lbm_batch *b = nullptr;
+    const std::vector<char> mem = batch_memory(&b, &stream);
+    const int id[3] = {submit(b, params(40, 400, LBM_FP64), 20), submit(b, params(40, 100, LBM_FP32), 20),
+                       submit(b, params(40, 10, LBM_FP16DEV), 20)};
+    CHECK(lbm_batch_step(b, 8) == LBM_OK);
+    fail_graph_launch = failing;
+    CHECK(lbm_batch_step(b, 8) == LBM_EDEVICE);
+    int64_t left = -1;
+    for (int i = 0; i < 3; ++i) {
+      CHECK(readable(b, id[i]) == (i >= failing));
+      CHECK(lbm_batch_remaining(b, id[i], &left) == LBM_OK);
+      CHECK(left == (i >= failing ? 12 : 0));  // those that lost their state take no more steps
+    }
+    CHECK(lbm_batch_step(b, 12) == LBM_OK);
+    for (int i = 0; i < 3; ++i) {
+      CHECK(readable(b, id[i]) == (i >= failing));
+      CHECK(lbm_batch_remaining(b, id[i], &left) == LBM_OK && left == 0);
+      CHECK(lbm_batch_retire(b, id[i]) == LBM_OK);
+    }
+    lbm_batch_destroy(b);
+  }
+}
+
 int main(int argc, char **argv) {
   const std::map<std::string, std::function<void()>> checks = {
       {"other_device", other_device},
       {"other_device_batch", other_device_batch},
+      {"failed_chunk", failed_chunk},
   };
   const auto it = argc > 1 ? checks.find(argv[1]) : checks.end();
   if (it == checks.end()) return 2;
