@@ -4457,7 +4457,7 @@ lbm_status get_graph(lbm_batch *b, int K, const int *variants, int n, hipGraphEx
 // The streams and events of the first `lanes` lanes, on the device of the
 // caller's stream, whatever device is current: its events are recorded there.
 hipError_t make_lanes(lbm_batch *b, int lanes) {
-  if (b->tie[lanes - 1]) return hipSuccess;
+  if (b->tie[lanes - 1]) return hipSuccess;  // made last
   int dev = 0;
   hipError_t e = hipStreamGetDevice(b->stream, &dev);
   if (e != hipSuccess) return e;
@@ -4506,14 +4506,16 @@ lbm_status launch_chunk(lbm_batch *b, int K) {
     }
     if (cap != hipStreamCaptureStatusNone) lanes = 1;
   }
+  if (lanes > 1 && make_lanes(b, lanes) != hipSuccess) {  // none to be had: one after the other
+    (void)hipGetLastError();
+    lanes = 1;
+  }
   hipGraphExec_t graph[kClasses];
   const int graphs = lanes > 1 ? present : 1;
   for (int i = 0; i < graphs; ++i) {
     const lbm_status st = get_graph(b, K, order + i, lanes > 1 ? 1 : present, &graph[i]);
     if (st != LBM_OK) return st;
   }
-  if (lanes > 1) e = make_lanes(b, lanes);
-  if (e != hipSuccess) return bhip(b, e, "creating the batch's streams");
   if (lanes > 1) e = hipEventRecord(b->tie[0], b->stream);
   for (int i = 1; i < lanes && e == hipSuccess; ++i)
     e = hipStreamWaitEvent(b->lane[i], b->tie[0], 0);

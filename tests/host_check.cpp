@@ -145,11 +145,29 @@ static void failed_chunk() {
   }
 }
 
+// Where no more streams are to be had, a batch steps on the caller's alone.
+static void no_more_streams() {
+  for (const int failures : {1, 2}) {
+    Stream stream{0};
+    lbm_batch *b = nullptr;
+    const std::vector<char> mem = batch_memory(&b, &stream);
+    submit(b, params(40, 30, LBM_FP64), 24);
+    submit(b, params(40, 20, LBM_FP32), 24);
+    submit(b, params(40, 10, LBM_FP16DEV), 24);
+    fail_stream_create = failures;
+    for (int i = 0; i < 3; ++i) CHECK(lbm_batch_step(b, 8) == LBM_OK);
+    fail_stream_create = 0;
+    lbm_batch_destroy(b);
+    CHECK(streams == 0 && events == 0);
+  }
+}
+
 int main(int argc, char **argv) {
   const std::map<std::string, std::function<void()>> checks = {
       {"other_device", other_device},
       {"other_device_batch", other_device_batch},
       {"failed_chunk", failed_chunk},
+      {"no_more_streams", no_more_streams},
   };
   const auto it = argc > 1 ? checks.find(argv[1]) : checks.end();
   if (it == checks.end()) return 2;
