@@ -3968,10 +3968,14 @@ lbm_status lbm_step(lbm_handle *h, int64_t nsteps) {
     }
     return LBM_OK;
   };
+  // The launches are as many as the steps, but for an even number: each goes
+  // from one copy of the state to the other, and steps that a caller captures
+  // and replays have to end on the copy that as many single steps end on.
   if (h->block_steps > 0 && left > 1) {
-    int64_t launches = (left + h->block_steps - 1) / h->block_steps;
-    if (flips && launches % 2) launches += launches < left ? 1 : -1;  // the rest goes in place
-    const lbm_status st = alternate(launches, h->block_steps == 1 ? launches : left,
+    const int64_t steps = flips ? left - left % 2 : left;  // the odd one goes in place
+    int64_t launches = (steps + h->block_steps - 1) / h->block_steps;
+    launches += (steps - launches) % 2;
+    const lbm_status st = alternate(launches, steps,
                                     [&](const BlockLaunch &l) { return run_block(h, l); });
     if (st != LBM_OK) return st;
   } else if (h->pair_tiles > 0) {

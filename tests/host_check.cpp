@@ -162,12 +162,40 @@ static void no_more_streams() {
   }
 }
 
+// n steps leave the two copies of the state as n launches of one step would,
+// so that steps that are captured and replayed start from the right one; and
+// the launches that move the previous velocity come in even numbers.
+static void launch_parity() {
+  for (const int precision : {LBM_FP64, LBM_FP32, LBM_FP16DEV})
+    for (const int flow : {LBM_FLOW_NS, LBM_FLOW_PRESCRIBED})
+      for (const int side : {20, 64, 100, 150, 240, 330, 720}) {
+        lbm_params p = params(side, side, precision);
+        p.flow = flow;
+        Sim s(p);
+        CHECK(s.init() == LBM_OK);
+        for (int n = 1; n <= 24; ++n) {
+          launched.clear();
+          CHECK(lbm_step(s.h, n) == LBM_OK);
+          const int single = launches("step_kernel"), block = launches("block_kernel"),
+                    pair = launches("pair_kernel"), all = single + block + pair;
+          CHECK(all == int(launched.size()) && all <= n && single + 3 * block + 2 * pair >= n);
+          if (all % 2 != n % 2) {
+            std::printf("precision %d, flow %d, %d^2: %d steps, %d launches\n", precision, flow,
+                        side, n, all);
+            std::exit(1);
+          }
+          if (precision != LBM_FP16DEV && flow == LBM_FLOW_NS) CHECK((block + pair) % 2 == 0);
+        }
+      }
+}
+
 int main(int argc, char **argv) {
   const std::map<std::string, std::function<void()>> checks = {
       {"other_device", other_device},
       {"other_device_batch", other_device_batch},
       {"failed_chunk", failed_chunk},
       {"no_more_streams", no_more_streams},
+      {"launch_parity", launch_parity},
   };
   const auto it = argc > 1 ? checks.find(argv[1]) : checks.end();
   if (it == checks.end()) return 2;
