@@ -3324,8 +3324,12 @@ hipError_t transfer(lbm_handle *h, const Piece *pieces, int npieces, bool planes
   // ones are cut where the caller's memory passes from one huge page to the
   // next: two workers that touch one page first would both clear it.
   const bool single = span <= kChunkBytes;
+  // The cuts are whole doubles from the start of the piece, which may stand
+  // on any address: `check` sees every value whole.
   auto first_part = [&](const Piece &p) {
-    return std::min(p.bytes, kChunkBytes - reinterpret_cast<uintptr_t>(p.host) % kChunkBytes);
+    const size_t to_page =
+        (kChunkBytes - reinterpret_cast<uintptr_t>(p.host) % kChunkBytes) / 8 * 8;
+    return std::min(p.bytes, to_page ? to_page : kChunkBytes);
   };
   auto parts_of = [&](const Piece &p) {
     return 1 + (long long)((p.bytes - first_part(p) + kChunkBytes - 1) / kChunkBytes);
@@ -3908,7 +3912,8 @@ lbm_status lbm_init_fields(lbm_handle *h, const double *phi, const double *psi,
   bool refused = false;
   hipError_t e = transfer(h, pieces, 4, true, true, nullptr, &refused,
                           [&](int piece, const char *at, size_t bytes) {
-    const double *const v = reinterpret_cast<const double *>(at);
+    typedef double anywhere __attribute__((aligned(1)));
+    const anywhere *const v = reinterpret_cast<const anywhere *>(at);
     const size_t m = bytes / sizeof(double);
     // |x| <= max rejects infinities and NaN alike; no branch per value
     int bad = 0, big = 0;

@@ -189,6 +189,46 @@ static void launch_parity() {
       }
 }
 
+// Initial fields anywhere in memory, on no multiple of 8 bytes too: valid ones
+// reach the device as they are, and a value that is not finite is refused
+// wherever it stands.
+static void unaligned_fields() {
+  for (const int side : {100, 400, 2100}) {  // one chunk, several, worker threads
+    Sim s(params(side, side, LBM_FP32));
+    const size_t bytes = s.n * sizeof(double), last = s.n - 1;
+    for (const size_t shift : {0, 3, 4}) {
+      std::vector<std::vector<char>> at(4, std::vector<char>(bytes + 8));
+      auto field = [&](int j) { return reinterpret_cast<const double *>(at[j].data() + shift); };
+      auto put = [&](int j, size_t k, double v) {
+        std::memcpy(at[j].data() + shift + k * sizeof v, &v, sizeof v);
+      };
+      auto init = [&] { return lbm_init_fields(s.h, field(0), field(1), field(2), field(3)); };
+      for (int j = 0; j < 4; ++j) std::memcpy(at[j].data() + shift, s.field[j].data(), bytes);
+      std::fill(s.mem.begin(), s.mem.end(), 0);
+      CHECK(init() == LBM_OK);
+      for (int j = 0; j < 4; ++j)
+        CHECK(memmem(s.mem.data(), s.mem.size(), s.field[j].data(), bytes));
+      for (const double v : {double(NAN), -double(INFINITY)})
+        for (const size_t k : {size_t(0), size_t(7), s.n / 2 + 1, last})
+          for (int j = 0; j < (side < 1000 ? 4 : 1); ++j) {
+            put(j, k, v);
+            CHECK(init() == LBM_EINVAL);
+            put(j, k, 0.5);
+          }
+      // around the ends of chunks
+      for (const size_t chunk : {size_t(1) << 21, size_t(3) << 21}) {
+        const size_t to = chunk - (reinterpret_cast<uintptr_t>(at[2].data()) + shift) % (1u << 21);
+        for (size_t k = to / 8; k < to / 8 + 3 && k > 1 && k <= last; ++k) {
+          put(2, k - 1, NAN);
+          CHECK(init() == LBM_EINVAL);
+          put(2, k - 1, 0.5);
+        }
+      }
+      CHECK(init() == LBM_OK);
+    }
+  }
+}
+
 int main(int argc, char **argv) {
   const std::map<std::string, std::function<void()>> checks = {
       {"other_device", other_device},
@@ -196,6 +236,7 @@ int main(int argc, char **argv) {
       {"failed_chunk", failed_chunk},
       {"no_more_streams", no_more_streams},
       {"launch_parity", launch_parity},
+      {"unaligned_fields", unaligned_fields},
   };
   const auto it = argc > 1 ? checks.find(argv[1]) : checks.end();
   if (it == checks.end()) return 2;
