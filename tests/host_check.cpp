@@ -229,6 +229,54 @@ static void unaligned_fields() {
   }
 }
 
+// Pinned memory of the caller's is copied to and from directly: the device
+// reaches it at the rate of the link without staging.
+static void pinned_memory() {
+  for (const int side : {64, 400, 2100}) {
+    Sim s(params(side, side, LBM_FP32));
+    const size_t bytes = s.n * sizeof(double);
+    std::vector<char *> made;
+    auto pin = [&](size_t n) {
+      void *p = nullptr;
+      CHECK(hipHostMalloc(&p, n, 0) == kOk);
+      made.push_back(static_cast<char *>(p));
+      return made.back();
+    };
+    double *f[5];
+    for (auto &p : f) p = reinterpret_cast<double *>(pin(bytes));
+    char *state = pin(s.state.size());
+    for (int j = 0; j < 4; ++j) std::memcpy(f[j], s.field[j].data(), bytes);
+    const size_t before = pinned_made;
+    auto direct = [&](size_t n) {  // that many bytes, all between the caller and the device
+      size_t sum = 0;
+      for (const Copy &c : copied)
+        for (const char *m : made)
+          if ((c.dst >= m && c.dst < m + pinned[const_cast<char *>(m)]) ||
+              (c.src >= m && c.src < m + pinned[const_cast<char *>(m)]))
+            sum += c.n;
+      copied.clear();
+      return sum == n && pinned_made == before;
+    };
+    copied.clear();
+    CHECK(lbm_init_fields(s.h, f[0], f[1], f[2], f[3]) == LBM_OK);
+    CHECK(direct(4 * bytes));
+    std::fill(f[0], f[0] + s.n, 0.0);
+    CHECK(lbm_read_fields(s.h, f[0], f[1], f[2], f[3], f[4]) == LBM_OK);
+    CHECK(direct(5 * bytes));
+    CHECK(!std::memcmp(f[0], s.field[0].data(), bytes));
+    CHECK(lbm_read_fields(s.h, nullptr, f[1], nullptr, nullptr, nullptr) == LBM_OK);
+    CHECK(direct(bytes));
+    CHECK(lbm_get_state(s.h, state, s.state.size()) == LBM_OK);
+    CHECK(direct(s.state.size() - sizeof(int64_t)));
+    CHECK(lbm_set_state(s.h, state, s.state.size()) == LBM_OK);
+    CHECK(direct(s.state.size() - sizeof(int64_t)));
+    f[2][s.n - 1] = NAN;
+    CHECK(lbm_init_fields(s.h, f[0], f[1], f[2], f[3]) == LBM_EINVAL);
+    CHECK(direct(2 * bytes));  // the fields before it, to scratch
+    for (char *m : made) CHECK(hipHostFree(m) == kOk);
+  }
+}
+
 int main(int argc, char **argv) {
   const std::map<std::string, std::function<void()>> checks = {
       {"other_device", other_device},
@@ -237,6 +285,7 @@ int main(int argc, char **argv) {
       {"no_more_streams", no_more_streams},
       {"launch_parity", launch_parity},
       {"unaligned_fields", unaligned_fields},
+      {"pinned_memory", pinned_memory},
   };
   const auto it = argc > 1 ? checks.find(argv[1]) : checks.end();
   if (it == checks.end()) return 2;

@@ -38,7 +38,11 @@ inline size_t pinned_made = 0;                       // bytes ever allocated
 inline int streams = 0, events = 0, graphs = 0;      // live objects
 inline int fail_graph_launch = -1;  // that launch of a graph fails (counted down)
 inline int fail_stream_create = 0;  // so many creations fail
-inline std::vector<const Stream *> waited;           // hipStreamSynchronize
+struct Copy {
+  const char *dst, *src;
+  size_t n;
+};
+inline std::vector<Copy> copied;  // hipMemcpyAsync, in order
 inline Dim3 cfg_grid, cfg_block;
 inline size_t cfg_shared;
 inline void *cfg_stream;
@@ -113,7 +117,22 @@ int hipHostFree(void *p) {
   return kOk;
 }
 int hipMemcpyAsync(void *dst, const void *src, size_t n, int, void *) {
+  Lock lock(mu);
+  copied.push_back({static_cast<const char *>(dst), static_cast<const char *>(src), n});
   std::memcpy(dst, src, n);
+  return kOk;
+}
+struct Attributes {
+  int type, device;
+  void *device_pointer, *host_pointer;
+  int managed;
+  unsigned flags;
+};
+int hipPointerGetAttributes(Attributes *a, const void *p) {
+  Lock lock(mu);
+  std::memset(a, 0, sizeof *a);  // type 0: memory that the runtime does not know
+  for (const auto &m : pinned)
+    if (p >= m.first && p < m.first + m.second) a->type = 1;
   return kOk;
 }
 int hipMemsetAsync(void *dst, int v, size_t n, void *) {
@@ -136,11 +155,7 @@ int hipStreamGetDevice(void *s, int *d) { return *d = device_of(s), kOk; }
 int hipStreamIsCapturing(void *s, int *status) {
   return *status = s && static_cast<Stream *>(s)->capturing, kOk;
 }
-int hipStreamSynchronize(void *s) {
-  Lock lock(mu);
-  waited.push_back(static_cast<Stream *>(s));
-  return kOk;
-}
+int hipStreamSynchronize(void *) { return kOk; }
 int hipEventCreateWithFlags(void **e, unsigned) {
   Lock lock(mu);
   ++events;
