@@ -3180,6 +3180,18 @@ constexpr int kWorkers = 6;
 // threads, 17 direct).
 constexpr size_t kThreadedBytes = 32u << 20;
 
+// To the device, staging without threads pays for initial fields of up to
+// kOneWrite (one copy instead of four) and of more than kManyWrites (their
+// check goes on while the chunk before is copied).  Between these, and for a
+// checkpoint, it is one more pass over host memory.  Directly and through
+// staging: initial fields of 128^2 (0.5 MB) 0.075 and 0.060 ms, 192^2 0.092
+// and 0.091, 288^2 0.13 and 0.19, 576^2 (10.6 MB) 0.46 and 0.47, 768^2 0.77
+// and 0.73; float32 checkpoints of 160^2 0.13 and 0.17, 384^2 0.50 and 0.53,
+// 512^2 (27 MB the largest part) 0.86 and 0.86, 576^2 with threads 1.31 and
+// 1.12.
+constexpr size_t kOneWrite = 1u << 20;
+constexpr size_t kManyWrites = 12u << 20;
+
 // Asks for the whole pages of [mem, mem + n), which is about to be written, in
 // one call: new pages taken one fault at a time cost 0.45 us each.  Does
 // nothing where the kernel does not know the request.
@@ -3315,10 +3327,14 @@ bool known_memory(const void *p) {
   return false;
 }
 
+hipError_t clear_flag(lbm_handle *h) {
+  return hipMemsetAsync(flagp(h), 0, sizeof(int), h->stream);
+}
+
 // transfer() without staging.
 template <class Check>
-hipError_t copy_directly(lbm_handle *h, const Piece *pieces, int npieces, bool to_device, int *flag,
-                         bool *refused, Check check) {
+hipError_t copy_directly(lbm_handle *h, const Piece *pieces, int npieces, bool planes,
+                         bool to_device, int *flag, bool *refused, Check check) {
   hipError_t e = hipSuccess;
   if (flag) {
     e = hipMemcpyAsync(flag, flagp(h), sizeof(int), hipMemcpyDeviceToHost, h->stream);
@@ -3335,6 +3351,7 @@ hipError_t copy_directly(lbm_handle *h, const Piece *pieces, int npieces, bool t
                   : hipMemcpyAsync(pieces[i].host, pieces[i].dev, pieces[i].bytes,
                                    hipMemcpyDeviceToHost, h->stream);
   }
+  if (e == hipSuccess && to_device && !planes) e = clear_flag(h);
   const hipError_t last = hipStreamSynchronize(h->stream);
   return e != hipSuccess ? e : last;
 }
@@ -3343,7 +3360,8 @@ hipError_t copy_directly(lbm_handle *h, const Piece *pieces, int npieces, bool t
 // them.  From the device: the sticky flag is read first (*flag), and nothing
 // reaches the caller's memory if it is set.  To the device: `check` sees all
 // of the host memory; if it refuses some, the copy ends (*refused).  planes:
-// the pieces are scratch planes one after another, whose gaps may be copied.
+// the pieces are scratch planes one after another, whose gaps may be copied;
+// without, they are a checkpoint, and the sticky flag is cleared behind it.
 template <class Check>
 hipError_t transfer(lbm_handle *h, const Piece *pieces, int npieces, bool planes, bool to_device,
                     int *flag, bool *refused, Check check) {
@@ -3352,12 +3370,17 @@ hipError_t transfer(lbm_handle *h, const Piece *pieces, int npieces, bool planes
   // 3.19 and 4.39; initial fields of 1448^2 1.87 and 2.94.
   for (int i = 0; i < npieces; ++i)
     if (known_memory(pieces[i].host))
-      return copy_directly(h, pieces, npieces, to_device, flag, refused, check);
+      return copy_directly(h, pieces, npieces, planes, to_device, flag, refused, check);
   if (npieces == 0) planes = false;
   size_t total = 0;
   for (int i = 0; i < npieces; ++i) total += pieces[i].bytes;
   const size_t span = planes ? size_t(pieces[npieces - 1].dev + pieces[npieces - 1].bytes -
                                       pieces[0].dev) : total;
+  size_t largest = 0;
+  for (int i = 0; i < npieces; ++i) largest = std::max(largest, pieces[i].bytes);
+  int threads = largest >= kThreadedBytes ? kWorkers : 0;
+  if (to_device && threads == 0 && !(planes && (span <= kOneWrite || span > kManyWrites)))
+    return copy_directly(h, pieces, npieces, planes, to_device, flag, refused, check);
   // Small transfers are one chunk, scratch planes one device copy.  Larger
   // ones are cut where the caller's memory passes from one huge page to the
   // next: two workers that touch one page first would both clear it.
@@ -3380,7 +3403,7 @@ hipError_t transfer(lbm_handle *h, const Piece *pieces, int npieces, bool planes
   if (hipStreamGetDevice(h->stream, &device) != hipSuccess ||
       !g_staging.take(kStagingHead + (single ? span : slots * kChunkBytes), device, &st)) {
     (void)hipGetLastError();  // no staging to be had
-    return copy_directly(h, pieces, npieces, to_device, flag, refused, check);
+    return copy_directly(h, pieces, npieces, planes, to_device, flag, refused, check);
   }
   auto slot = [&](long long k) { return st.mem + kStagingHead + size_t(k % slots) * kChunkBytes; };
   // f(piece, offset in it, bytes, offset in the slot) for the parts of chunk
@@ -3404,9 +3427,6 @@ hipError_t transfer(lbm_handle *h, const Piece *pieces, int npieces, bool planes
     }
     return true;
   };
-  size_t largest = 0;
-  for (int i = 0; i < npieces; ++i) largest = std::max(largest, pieces[i].bytes);
-  int threads = largest >= kThreadedBytes ? kWorkers : 0;
   auto host_part = [&](long long k) {  // between the slot and the caller's memory
     return each_part(k, [&](int i, size_t off, size_t n, size_t in_slot) {
       char *const mem = pieces[i].host + off;
@@ -3528,6 +3548,7 @@ hipError_t transfer(lbm_handle *h, const Piece *pieces, int npieces, bool planes
   for (int w = 0; w < started; ++w) pool[w].join();
   if (refused) *refused = bad;
   // nothing of the staging may be in flight when it goes back
+  if (e == hipSuccess && to_device && !planes) e = clear_flag(h);
   if (to_device || e != hipSuccess || (flag && *flag)) {
     const hipError_t last = hipStreamSynchronize(h->stream);
     if (e == hipSuccess) e = last;
@@ -3951,7 +3972,7 @@ lbm_status lbm_init_fields(lbm_handle *h, const double *phi, const double *psi,
   h->valid = false;
   h->cur = 0;
   e = run_init(h);
-  if (e == hipSuccess) e = hipMemsetAsync(flagp(h), 0, sizeof(int), h->stream);
+  if (e == hipSuccess) e = clear_flag(h);
   if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
   if (e != hipSuccess) return hip_check(h, e, "initialising");
   h->step = 0;
@@ -4174,9 +4195,7 @@ lbm_status lbm_set_state(lbm_handle *h, const void *host_buf, size_t bytes) {
   h->cur = 0;
   const StatePieces parts(h, 0, static_cast<char *>(const_cast<void *>(host_buf)));
   bool refused = false;
-  hipError_t e = transfer(h, parts.p, 3, false, true, nullptr, &refused, NoCheck{});
-  if (e == hipSuccess) e = hipMemsetAsync(flagp(h), 0, sizeof(int), h->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
+  const hipError_t e = transfer(h, parts.p, 3, false, true, nullptr, &refused, NoCheck{});
   if (e != hipSuccess) return hip_check(h, e, "restoring state");
   h->step = step;
   h->valid = true;

@@ -277,6 +277,36 @@ static void pinned_memory() {
   }
 }
 
+// Whether a call copies through the library's pinned memory.
+static bool staged(const std::function<lbm_status()> &call) {
+  copied.clear();
+  CHECK(call() == LBM_OK);
+  for (const Copy &c : copied)
+    for (const auto &m : pinned)
+      if (c.n > sizeof(int) && ((c.dst >= m.first && c.dst < m.first + m.second) ||
+                                (c.src >= m.first && c.src < m.first + m.second)))
+        return true;
+  return false;
+}
+
+// To the device, only those transfers go through staging that gain.
+static void staged_writes() {
+  struct Expected {
+    int side;
+    bool init, set;
+  };
+  for (const Expected &x : {Expected{32, true, false}, {128, true, false}, {181, true, false},
+                            {182, false, false}, {288, false, false}, {512, false, false},
+                            {620, false, true}, {630, true, true}, {1100, true, true}}) {
+    Sim s(params(x.side, x.side, LBM_FP32));
+    CHECK(s.init() == LBM_OK);
+    for (int i = 0; i < 3; ++i) CHECK(s.read() == LBM_OK);
+    CHECK(lbm_get_state(s.h, s.state.data(), s.state.size()) == LBM_OK);
+    CHECK(staged([&] { return s.init(); }) == x.init);
+    CHECK(staged([&] { return lbm_set_state(s.h, s.state.data(), s.state.size()); }) == x.set);
+  }
+}
+
 int main(int argc, char **argv) {
   const std::map<std::string, std::function<void()>> checks = {
       {"other_device", other_device},
@@ -286,6 +316,7 @@ int main(int argc, char **argv) {
       {"launch_parity", launch_parity},
       {"unaligned_fields", unaligned_fields},
       {"pinned_memory", pinned_memory},
+      {"staged_writes", staged_writes},
   };
   const auto it = argc > 1 ? checks.find(argv[1]) : checks.end();
   if (it == checks.end()) return 2;
