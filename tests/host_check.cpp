@@ -289,6 +289,28 @@ static bool staged(const std::function<lbm_status()> &call) {
   return false;
 }
 
+// A program whose first two transfers are small makes no staging: what it
+// costs they would not give back.
+static void first_transfers() {
+  for (int again = 0; again < 2; ++again)
+    for (const int side : {32, 100, 256, 457, 458, 700}) {  // five fields of 458^2 pass 8 MiB
+      Sim s(params(side, side, LBM_FP32));
+      auto init = [&] { return s.init(); };
+      auto read = [&] { return s.read(); };
+      auto get = [&] { return lbm_get_state(s.h, s.state.data(), s.state.size()); };
+      CHECK(pinned.empty());
+      CHECK(staged(init) == (side == 700));
+      CHECK(staged(read) == (side >= 458));
+      // the third; for 256^2 the second, since its initial fields never are
+      CHECK(staged(get) == (side != 256));
+      CHECK(staged(read));
+      Sim other(params(64, 64, LBM_FP64));  // staging that is there serves all
+      CHECK(staged([&] { return other.init(); }));
+      CHECK(staged(get));
+    }
+  CHECK(pinned.empty() && events == 0);
+}
+
 // To the device, only those transfers go through staging that gain.
 static void staged_writes() {
   struct Expected {
@@ -316,6 +338,7 @@ int main(int argc, char **argv) {
       {"launch_parity", launch_parity},
       {"unaligned_fields", unaligned_fields},
       {"pinned_memory", pinned_memory},
+      {"first_transfers", first_transfers},
       {"staged_writes", staged_writes},
   };
   const auto it = argc > 1 ? checks.find(argv[1]) : checks.end();
