@@ -3192,6 +3192,16 @@ constexpr size_t kThreadedBytes = 32u << 20;
 constexpr size_t kOneWrite = 1u << 20;
 constexpr size_t kManyWrites = 12u << 20;
 
+// Making staging costs as much as it saves in several small transfers, so a
+// program's first two of up to kAtOnce, say the initial fields and the result
+// of one solve, go without (StagingPool::take); but not fields that fit in the
+// smallest staging.  Create, init, read, destroy, directly and with staging:
+// float32 32^2 0.160 and 0.134 ms, 64^2 0.160 and 0.153, 256^2 (2.6 MB read)
+// 0.32 and 0.50, 320^2 0.42 and 0.55, 384^2 0.64 and 0.73, 512^2 (10.5 MB)
+// 1.07 and 0.94; a checkpoint of 160^2 set and got 0.36 and 0.47.
+constexpr size_t kAtOnce = 8u << 20;
+constexpr size_t kLeastStaging = 1u << 18;
+
 // Asks for the whole pages of [mem, mem + n), which is about to be written, in
 // one call: new pages taken one fault at a time cost 0.45 us each.  Does
 // nothing where the kernel does not know the request.
@@ -3251,9 +3261,9 @@ class StagingPool {
     }
     while (n > 0) release(all[--n]);
   }
-  // A buffer of at least `bytes` for a stream of `device`, to transfer `total`
-  // bytes (false: none to be had, or none worth making).
-  bool take(size_t bytes, int device, size_t total, Staging *out) {
+  // A buffer of at least `bytes` for a stream of `device` (false: none to be
+  // had, or for this `small` transfer none worth making).
+  bool take(size_t bytes, int device, bool small, Staging *out) {
     {
       std::lock_guard<std::mutex> lock(mu_);
       for (int i = 0; i < count_; ++i)
@@ -3262,7 +3272,7 @@ class StagingPool {
           idle_[i] = idle_[--count_];
           return true;
         }
-      if (total < kAtOnce && small_ < kSmallOnes) {
+      if (small && small_ < kSmallOnes) {
         ++small_;
         return false;
       }
@@ -3270,7 +3280,7 @@ class StagingPool {
     const OnDevice on(device);
     Staging s;
     s.device = device;
-    s.bytes = size_t(1) << 18;
+    s.bytes = kLeastStaging;
     while (s.bytes < bytes) s.bytes *= 2;
     s.bytes = std::min(s.bytes, kStagingHead + kSlots * kChunkBytes);
     bool ok = on.ok() &&
@@ -3302,14 +3312,7 @@ class StagingPool {
 
  private:
   static constexpr int kIdle = 2;
-  // Making staging costs as much as it saves in several small transfers, so a
-  // program's first two, say the initial fields and the result of one solve,
-  // go without.  Create, init, read, destroy, directly and with staging:
-  // float32 256^2 (2.6 MB read) 0.35 and 0.50 ms, 320^2 0.46 and 0.55, 384^2
-  // 0.71 and 0.73, 512^2 (10.5 MB) 1.07 and 0.99, 1024^2 4.3 and 3.6; a
-  // checkpoint of 160^2 set and got 0.37 and 0.47.
   static constexpr int kSmallOnes = 2;
-  static constexpr size_t kAtOnce = 8u << 20;
   int small_ = 0;  // those gone without since the first of the live handles
   static void release(Staging &s) {
     for (hipEvent_t e : s.done)
@@ -3415,8 +3418,10 @@ hipError_t transfer(lbm_handle *h, const Piece *pieces, int npieces, bool planes
   const int slots = int(std::min<long long>(chunks, kSlots));
   Staging st;
   int device = -1;
+  const size_t bytes = kStagingHead + (single ? span : slots * kChunkBytes);
+  const bool small = span < kAtOnce && !(planes && bytes <= kLeastStaging);
   if (hipStreamGetDevice(h->stream, &device) != hipSuccess ||
-      !g_staging.take(kStagingHead + (single ? span : slots * kChunkBytes), device, span, &st)) {
+      !g_staging.take(bytes, device, small, &st)) {
     (void)hipGetLastError();  // no staging to be had
     return copy_directly(h, pieces, npieces, planes, to_device, flag, refused, check);
   }
