@@ -2912,6 +2912,7 @@ struct lbm_handle {
   int pair_tiles;      // the plan in use: 0 under a tile height set by the caller
   int block_plan;      // steps per launch of the block kernel (plan_block_steps)
   int block_steps;     // the plan in use: 0 under a tile height set by the caller
+  bool block_whole;    // launches of fewer steps than block_steps do not pay
   std::string kernel;  // the step kernel variant, as a profiler names it
   std::string err;
   double *fixed_scratch;  // this device's copy of the static read-back scratch
@@ -3661,11 +3662,15 @@ hipError_t run_pair(lbm_handle *h, const BlockLaunch &l, int *waves_per_cu = nul
 //    6.33 with 1 and 7.9 for lbm_step_kernel; 176^2, 324 blocks, 6.67 against
 //    6.53 with 1.  float32 with the Navier-Stokes flow also gains with two
 //    rounds: 320x300, 960 blocks, 7.05 us against 7.68; 360x300, 1080
-//    blocks, 9.09 against 7.73.
+//    blocks, 9.09 against 7.73.  There a launch of one step may take two
+//    rounds as well and then costs more than lbm_step_kernel's (320^2, 529
+//    blocks: 10.3 us against 7.8), which takes what whole launches leave
+//    (h->block_whole).
 //  * 1, if they are all resident: float64 210^2, 225 blocks, 7.01 us against
 //    8.17; float16 176^2, 195 blocks, 6.86 against 8.39; 210^2, 270 blocks,
 //    11.2 against 8.56.
-int plan_block_steps(const lbm_handle *h, int cus, int resident) {
+int plan_block_steps(lbm_handle *h, int cus, int resident) {
+  h->block_whole = block_count(h->p, 1) > resident;
   if (cus <= 0 || resident <= 0) return 0;
   if (block_count(h->p, kBlockMaxSteps) <= cus) return kBlockMaxSteps;
   const int rounds = h->p.precision == LBM_FP32 && h->ns ? 2 : 1;
@@ -4038,7 +4043,8 @@ lbm_status lbm_step(lbm_handle *h, int64_t nsteps) {
   // from one copy of the state to the other, and steps that a caller captures
   // and replays have to end on the copy that as many single steps end on.
   if (h->block_steps > 0 && left > 1) {
-    const int64_t steps = flips ? left - left % 2 : left;  // the odd one goes in place
+    int64_t steps = flips ? left - left % 2 : left;  // the odd one goes in place
+    if (h->block_whole) steps -= steps % (2 * h->block_steps);
     int64_t launches = (steps + h->block_steps - 1) / h->block_steps;
     launches += (steps - launches) % 2;
     const lbm_status st = alternate(launches, steps,

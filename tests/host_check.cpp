@@ -189,6 +189,23 @@ static void launch_parity() {
       }
 }
 
+// On grids whose blocks take two rounds even with one step (float32, 522 to
+// 552 blocks on 512 slots), a launch of the block kernel takes two steps or is
+// not made: one of a single step is slower than lbm_step_kernel.
+static void whole_launches() {
+  const int sides[][2] = {{320, 320}, {330, 310}, {400, 250}};
+  for (const auto &side : sides) {
+    Sim s(params(side[0], side[1], LBM_FP32));
+    CHECK(s.init() == LBM_OK);
+    for (int n = 1; n <= 13; ++n) {
+      launched.clear();
+      CHECK(lbm_step(s.h, n) == LBM_OK);
+      const int single = launches("step_kernel"), block = launches("block_kernel");
+      CHECK(block == n / 4 * 2 && single + 2 * block == n && launches("pair_kernel") == 0);
+    }
+  }
+}
+
 // Initial fields anywhere in memory, on no multiple of 8 bytes too: valid ones
 // reach the device as they are, and a value that is not finite is refused
 // wherever it stands.
@@ -336,6 +353,7 @@ int main(int argc, char **argv) {
       {"failed_chunk", failed_chunk},
       {"no_more_streams", no_more_streams},
       {"launch_parity", launch_parity},
+      {"whole_launches", whole_launches},
       {"unaligned_fields", unaligned_fields},
       {"pinned_memory", pinned_memory},
       {"first_transfers", first_transfers},

@@ -27,7 +27,7 @@ def host_check(tmp_path_factory):
 
 
 @pytest.mark.parametrize("check", ["other_device", "other_device_batch", "failed_chunk",
-                                   "no_more_streams", "launch_parity",
+                                   "no_more_streams", "launch_parity", "whole_launches",
                                    "unaligned_fields", "pinned_memory", "first_transfers",
                                    "staged_writes"])
 def test_host_code(host_check, check):
