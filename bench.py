@@ -44,16 +44,6 @@ def algorithmic_bytes_per_site(precision: str) -> int:
     return 2 * 26 * STORE_BYTES[precision] + 2 * fields * FIELD_BYTES[precision]
 
 
-def field_kernel(step_kernel: str, precision: str, rows: int) -> tuple:
-    """The kernel that steps the 2048x2048 field, and its steps per launch:
-    with float64 and float32 storage lbm_step takes two steps per launch
-    there, unless the caller has set a tile height."""
-    if precision == "fp16dev" or rows:
-        return step_kernel, 1
-    storage, _columns, *rest = step_kernel[len("lbm_step_kernel<"):-1].split(", ")
-    return f"lbm_pair_kernel<{', '.join([storage] + rest[:2])}>", 2
-
-
 def launches_of(steps: int, steps_per_launch: int) -> int:
     """Launches that `steps` steps take: the two-step kernel's come in even
     numbers, and the steps left over are one launch each."""
@@ -498,7 +488,7 @@ def main():
     # A launch reads and writes the whole state once, whatever its steps: the
     # roofline counts the bytes that the launches move, not those that one
     # launch per step would.
-    kernel, steps_per_launch = field_kernel(sim.step_kernel_name(), args.precision, args.rows)
+    kernel, steps_per_launch = sim.step_plan()
     launches = launches_of(args.steps, steps_per_launch)
     per_launch_ms = ms_events / launches
     achieved = bps * sites / (per_launch_ms * 1e-3) / 1e9

@@ -273,6 +273,14 @@ lbm_status lbm_get_tile_plan(const lbm_handle *h, int32_t *plan);
  * "lbm_step_kernel" for a NULL handle. */
 const char *lbm_step_kernel_name(const lbm_handle *h);
 
+/* The kernel that lbm_step launches for this handle where a call's steps
+ * allow several per launch, and how many a launch takes at most (*steps, may
+ * be NULL): "lbm_block_kernel<storage, r != 1, rho_A != rho_B, Navier-Stokes
+ * velocity>" with 1 to 3, "lbm_pair_kernel<storage, r != 1, rho_A != rho_B>"
+ * with 2, or lbm_step_kernel_name with 1 where every step is a launch of its
+ * own.  "lbm_step_kernel", *steps untouched, for a NULL handle. */
+const char *lbm_step_plan(const lbm_handle *h, int32_t *steps);
+
 /* ----------------------------------------------------------------------
  * Batches: many independent simulations advanced together.
  *

@@ -2914,6 +2914,7 @@ struct lbm_handle {
   int block_steps;     // the plan in use: 0 under a tile height set by the caller
   bool block_whole;    // launches of fewer steps than block_steps do not pay
   std::string kernel;  // the step kernel variant, as a profiler names it
+  std::string kernel_of_several;  // the kernel of several steps per launch, if planned
   std::string err;
   double *fixed_scratch;  // this device's copy of the static read-back scratch
 };
@@ -3754,13 +3755,25 @@ void plan_tiles(lbm_handle *h) {
 // The template arguments of the step kernel run_step launches for h, in the
 // order a profiler prints them: storage, columns per lane, r != 1,
 // rho_A != rho_B, Navier-Stokes velocity.
+const char *storage_name_of(const lbm_handle *h, bool resident) {
+  return h->p.precision == LBM_FP64   ? (resident ? "F64C" : "F64")
+         : h->p.precision == LBM_FP32 ? (resident ? "F32C" : "F32")
+                                      : "F16";
+}
+const char *name_of(bool v) { return v ? "true" : "false"; }
 std::string kernel_name_of(const lbm_handle *h) {
-  const char *prec = h->p.precision == LBM_FP64   ? (h->resident ? "F64C" : "F64")
-                     : h->p.precision == LBM_FP32 ? (h->resident ? "F32C" : "F32")
-                                                  : "F16";
-  auto b = [](bool v) { return v ? "true" : "false"; };
-  return std::string("lbm_step_kernel<") + prec + ", " + std::to_string(sites_per_lane(h->p)) +
-         ", " + b(h->genr) + ", " + b(h->has_s) + ", " + b(h->ns) + ">";
+  return std::string("lbm_step_kernel<") + storage_name_of(h, h->resident) + ", " +
+         std::to_string(sites_per_lane(h->p)) + ", " + name_of(h->genr) + ", " +
+         name_of(h->has_s) + ", " + name_of(h->ns) + ">";
+}
+std::string kernel_of_several_of(const lbm_handle *h) {
+  if (h->block_plan > 0)
+    return std::string("lbm_block_kernel<") + storage_name_of(h, true) + ", " +
+           name_of(h->genr) + ", " + name_of(h->has_s && h->ns) + ", " + name_of(h->ns) + ">";
+  if (h->pair_plan > 0)
+    return std::string("lbm_pair_kernel<") + storage_name_of(h, h->resident) + ", " +
+           name_of(h->genr) + ", " + name_of(h->has_s) + ">";
+  return h->kernel;
 }
 
 // Wavefronts of h's step kernel the current device holds at once (0 if the
@@ -3953,6 +3966,7 @@ lbm_status lbm_create(const lbm_params *params, void *dev_ws, size_t ws_bytes,
   h->block_plan = h->block_steps = query_block_steps(h);
   h->pair_plan = h->pair_tiles = query_pair_tiles(h);
   h->kernel = kernel_name_of(h);
+  h->kernel_of_several = kernel_of_several_of(h);
   int dev = -1;
   h->fixed_scratch = hipStreamGetDevice(h->stream, &dev) == hipSuccess ? fixed_scratch_of(dev)
                                                                       : nullptr;
@@ -4262,6 +4276,13 @@ lbm_status lbm_get_tile_plan(const lbm_handle *h, int32_t *plan) {
   plan[1] = h->tail_rows;
   plan[2] = h->tail_h;
   return LBM_OK;
+}
+
+const char *lbm_step_plan(const lbm_handle *h, int32_t *steps) {
+  if (!h) return "lbm_step_kernel";
+  const bool several = h->block_steps > 0 || h->pair_tiles > 0;
+  if (steps) *steps = !several ? 1 : h->block_steps > 0 ? h->block_steps : 2;
+  return several ? h->kernel_of_several.c_str() : h->kernel.c_str();
 }
 
 const char *lbm_step_kernel_name(const lbm_handle *h) {

@@ -70,7 +70,7 @@ EXPORTS = ("lbm_workspace_bytes", "lbm_create", "lbm_init_fields", "lbm_step",
            "lbm_read_fields", "lbm_moments", "lbm_moments_async", "lbm_state_bytes",
            "lbm_get_state",
            "lbm_set_state", "lbm_destroy", "lbm_last_error", "lbm_set_tile_rows",
-           "lbm_get_tile_plan", "lbm_step_kernel_name")
+           "lbm_get_tile_plan", "lbm_step_kernel_name", "lbm_step_plan")
 
 _lib = None
 
@@ -112,6 +112,8 @@ def load(path: str = LIB_PATH):
     lib.lbm_get_tile_plan.argtypes = [H, ctypes.POINTER(ctypes.c_int32)]
     lib.lbm_step_kernel_name.argtypes = [H]
     lib.lbm_step_kernel_name.restype = ctypes.c_char_p
+    lib.lbm_step_plan.argtypes = [H, ctypes.POINTER(ctypes.c_int32)]
+    lib.lbm_step_plan.restype = ctypes.c_char_p
     for name in ("lbm_create", "lbm_init_fields", "lbm_step", "lbm_read_fields",
                  "lbm_moments", "lbm_moments_async", "lbm_get_state", "lbm_set_state",
                  "lbm_set_tile_rows", "lbm_get_tile_plan"):
@@ -314,6 +316,13 @@ class Simulation:
 
     def step_kernel_name(self) -> str:
         return self.lib.lbm_step_kernel_name(self._handle).decode()
+
+    def step_plan(self) -> tuple[str, int]:
+        """(kernel of several steps per launch, steps per launch at most);
+        the step kernel and 1 where every step is a launch of its own."""
+        steps = ctypes.c_int32()
+        name = self.lib.lbm_step_plan(self._handle, ctypes.byref(steps)).decode()
+        return name, steps.value
 
     def close(self):
         if getattr(self, "_handle", None):

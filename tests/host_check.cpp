@@ -189,6 +189,29 @@ static void launch_parity() {
       }
 }
 
+// Where the tall tiles of a band all run at once (2 workgroups of 4 wavefronts
+// on each of 256 compute units), the short ones at its end make no second
+// round.
+static void tile_plan() {
+  int cut = 0;
+  for (const int precision : {LBM_FP64, LBM_FP32})
+    for (int side = 200; side < 1100; side += 13) {
+      Sim s(params(side, side + 6, precision));
+      int32_t plan[3];
+      CHECK(lbm_get_tile_plan(s.h, plan) == LBM_OK);
+      const int columns = precision == LBM_FP32 && side % 2 == 0 ? 124 : 60;
+      const int strips = (side + columns - 1) / columns, round = 256 * 2 * 4 / (8 * strips);
+      const int band = (side + 6 + 7) / 8;
+      if (plan[0] == 1 || (band + plan[0] - 1) / plan[0] > round) continue;
+      if (precision == LBM_FP32 && plan[0] > 2) continue;  // tiles of 3 rows gain all the same
+      const int chunks = (band - plan[1] + plan[0] - 1) / plan[0] +
+                         (plan[1] + plan[2] - 1) / plan[2];
+      CHECK(chunks <= round);
+      cut += plan[1] > 0;
+    }
+  CHECK(cut > 5);  // plans with short tiles that fit
+}
+
 // On grids whose blocks take two rounds even with one step (float32, 522 to
 // 552 blocks on 512 slots), a launch of the block kernel takes two steps or is
 // not made: one of a single step is slower than lbm_step_kernel.
@@ -354,6 +377,7 @@ int main(int argc, char **argv) {
       {"no_more_streams", no_more_streams},
       {"launch_parity", launch_parity},
       {"whole_launches", whole_launches},
+      {"tile_plan", tile_plan},
       {"unaligned_fields", unaligned_fields},
       {"pinned_memory", pinned_memory},
       {"first_transfers", first_transfers},

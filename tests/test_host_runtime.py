@@ -27,10 +27,19 @@ def host_check(tmp_path_factory):
 
 
 @pytest.mark.parametrize("check", ["other_device", "other_device_batch", "failed_chunk",
-                                   "no_more_streams", "launch_parity", "whole_launches",
+                                   "no_more_streams", "launch_parity", "whole_launches", "tile_plan",
                                    "unaligned_fields", "pinned_memory", "first_transfers",
                                    "staged_writes"])
 def test_host_code(host_check, check):
     out = subprocess.run([host_check, check], capture_output=True, text=True, timeout=120)
     assert out.returncode == 0 and check + " ok" in out.stdout, (out.returncode, out.stdout,
                                                                  out.stderr)
+
+
+def test_step_plan_of_no_handle():
+    import ctypes
+
+    steps = ctypes.c_int32(7)
+    assert lbm.load().lbm_step_plan(None, ctypes.byref(steps)) == b"lbm_step_kernel"
+    assert steps.value == 7
+    assert lbm.load().lbm_step_plan(None, None) == b"lbm_step_kernel"
