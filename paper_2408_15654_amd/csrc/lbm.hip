@@ -2912,6 +2912,7 @@ struct lbm_handle {
   int pair_tiles;      // the plan in use: 0 under a tile height set by the caller
   int block_plan;      // steps per launch of the block kernel (plan_block_steps)
   int block_steps;     // the plan in use: 0 under a tile height set by the caller
+  bool of_batch;       // transfers of a batch's simulations always use staging
   bool block_whole;    // launches of fewer steps than block_steps do not pay
   std::string kernel;  // the step kernel variant, as a profiler names it
   std::string kernel_of_several;  // the kernel of several steps per launch, if planned
@@ -3193,6 +3194,9 @@ constexpr size_t kThreadedBytes = 32u << 20;
 // 1.12.
 constexpr size_t kOneWrite = 1u << 20;
 constexpr size_t kManyWrites = 12u << 20;
+// Not in a batch, whose simulations step meanwhile: with the joiners' initial
+// fields copied directly, the served burst of twelve float32 solves took 16 to
+// 20 ms (every other run 19 or more), through staging 15 to 16.6.
 
 // Making staging costs as much as it saves in several small transfers, so a
 // program's first two of up to kAtOnce, say the initial fields and the result
@@ -3399,7 +3403,8 @@ hipError_t transfer(lbm_handle *h, const Piece *pieces, int npieces, bool planes
   size_t largest = 0;
   for (int i = 0; i < npieces; ++i) largest = std::max(largest, pieces[i].bytes);
   int threads = largest >= kThreadedBytes ? kWorkers : 0;
-  if (to_device && threads == 0 && !(planes && (span <= kOneWrite || span > kManyWrites)))
+  if (to_device && threads == 0 && !h->of_batch &&
+      !(planes && (span <= kOneWrite || span > kManyWrites)))
     return copy_directly(h, pieces, npieces, planes, to_device, flag, refused, check);
   // Small transfers are one chunk, scratch planes one device copy.  Larger
   // ones are cut where the caller's memory passes from one huge page to the
@@ -3421,7 +3426,8 @@ hipError_t transfer(lbm_handle *h, const Piece *pieces, int npieces, bool planes
   Staging st;
   int device = -1;
   const size_t bytes = kStagingHead + (single ? span : slots * kChunkBytes);
-  const bool small = span < kAtOnce && !(planes && bytes <= kLeastStaging);
+  const bool small =
+      span < kAtOnce && !h->of_batch && !(planes && bytes <= kLeastStaging);
   if (hipStreamGetDevice(h->stream, &device) != hipSuccess ||
       !g_staging.take(bytes, device, small, &st)) {
     (void)hipGetLastError();  // no staging to be had
@@ -3965,6 +3971,7 @@ lbm_status lbm_create(const lbm_params *params, void *dev_ws, size_t ws_bytes,
   plan_tiles(h);
   h->block_plan = h->block_steps = query_block_steps(h);
   h->pair_plan = h->pair_tiles = query_pair_tiles(h);
+  h->of_batch = false;
   h->kernel = kernel_name_of(h);
   h->kernel_of_several = kernel_of_several_of(h);
   int dev = -1;
@@ -4737,6 +4744,7 @@ lbm_status lbm_batch_submit(lbm_batch *b, const lbm_params *params, const double
   lbm_handle *h = nullptr;
   lbm_status st = lbm_create(params, b->ws + off, bytes, b->admit, &h);
   if (st == LBM_OK) {
+    h->of_batch = true;
     st = lbm_init_fields(h, phi, psi, ux, uy);
     if (st != LBM_OK) {
       bfail(b, st, h->err);

@@ -351,6 +351,26 @@ static void first_transfers() {
   CHECK(pinned.empty() && events == 0);
 }
 
+// A batch's transfers all go through staging: other simulations step meanwhile.
+static void batch_transfers() {
+  Stream stream{0};
+  lbm_batch *b = nullptr;
+  std::vector<char> mem(size_t(800) << 20);
+  char *ws = mem.data() + (256 - reinterpret_cast<uintptr_t>(mem.data()) % 256) % 256;
+  CHECK(lbm_batch_create(8, ws, mem.size() - 256, &stream, &b) == LBM_OK);
+  for (const int side : {40, 200, 288, 512}) {
+    std::vector<double> f(size_t(side) * side);
+    int id = -1;
+    CHECK(staged([&] { return (id = submit(b, params(side, side, LBM_FP32), 4)) >= 0 ? LBM_OK : LBM_EINVAL; }));
+    CHECK(staged([&] {
+      return lbm_batch_read_fields(b, id, f.data(), nullptr, nullptr, nullptr, nullptr);
+    }));
+    CHECK(lbm_batch_retire(b, id) == LBM_OK);
+  }
+  lbm_batch_destroy(b);
+  CHECK(pinned.empty());
+}
+
 // To the device, only those transfers go through staging that gain.
 static void staged_writes() {
   struct Expected {
@@ -382,6 +402,7 @@ int main(int argc, char **argv) {
       {"pinned_memory", pinned_memory},
       {"first_transfers", first_transfers},
       {"staged_writes", staged_writes},
+      {"batch_transfers", batch_transfers},
   };
   const auto it = argc > 1 ? checks.find(argv[1]) : checks.end();
   if (it == checks.end()) return 2;

@@ -29,7 +29,7 @@ def host_check(tmp_path_factory):
 @pytest.mark.parametrize("check", ["other_device", "other_device_batch", "failed_chunk",
                                    "no_more_streams", "launch_parity", "whole_launches", "tile_plan",
                                    "unaligned_fields", "pinned_memory", "first_transfers",
-                                   "staged_writes"])
+                                   "staged_writes", "batch_transfers"])
 def test_host_code(host_check, check):
     out = subprocess.run([host_check, check], capture_output=True, text=True, timeout=120)
     assert out.returncode == 0 and check + " ok" in out.stdout, (out.returncode, out.stdout,
