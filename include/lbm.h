@@ -156,13 +156,19 @@ lbm_status lbm_create(const lbm_params *params, void *dev_ws, size_t ws_bytes,
 lbm_status lbm_init_fields(lbm_handle *h, const double *phi, const double *psi,
                            const double *ux, const double *uy);
 
-/* Advance nsteps >= 0 time steps: each is one launch of the fused
- * stream-collide kernel (pull streaming with half-way bounce-back, the
- * gradient stencils, forces, closures (32a)-(32b), and the three MRT
- * collisions of Eqs. (21), (25), (29) in moment space).  On a grid too small
- * to fill the device a launch takes up to three steps, on a large one with
- * float64 or float32 storage two steps (the same results); these launches
- * use the read-back scratch of the workspace meanwhile.  Asynchronous.
+/* Advance nsteps >= 0 time steps of the fused stream-collide kernels (pull
+ * streaming with half-way bounce-back, the gradient stencils, forces, closures
+ * (32a)-(32b), and the three MRT collisions of Eqs. (21), (25), (29) in moment
+ * space).  A launch takes one step, or several with the same results: up to
+ * three on a grid too small to fill the device, two on a large one with
+ * float64 or float32 storage, there in calls of four steps and more (of 4 k + r
+ * steps, r < 4 are launches of their own).  Launches of several steps use the
+ * read-back scratch of the workspace meanwhile.  Asynchronous.
+ * Only kernel launches are enqueued, so the call may be captured into a HIP
+ * graph.  The state is kept twice, and nsteps steps end on the copy that they
+ * started from if nsteps is even: a captured even number of steps may be
+ * replayed as it is, odd ones in turns that together are even.  The handle
+ * counts captured steps once, when they are captured.
  * Errors: LBM_EINVAL (nsteps < 0), LBM_ESTATE, LBM_EDEVICE. */
 lbm_status lbm_step(lbm_handle *h, int64_t nsteps);
 
@@ -293,15 +299,19 @@ const char *lbm_step_plan(const lbm_handle *h, int32_t *steps);
  * (storage precision; one or two columns per lane, two for float32 and
  * float16 storage with even nx; Navier-Stokes or prescribed flow; r == 1
  * or not; equal densities or not); a chunk of those launches is captured
- * once as a HIP graph and replayed.  The
+ * once as a HIP graph and replayed.  Variants do not touch each other: a
+ * chunk of four steps and more is a graph per variant, which run side by
+ * side.  The
  * arithmetic of each simulation is exactly that of lbm_step on its own
  * (bitwise), whatever the batch holds and whatever the schedule.
  *
  * Simulations join with lbm_batch_submit while others run (admitted as
  * workspace and ids allow) and leave with lbm_batch_retire, so a request
  * loop can keep the device busy with a changing set of solves.
- * All calls are made from one host thread; work goes to the stream given
- * to lbm_batch_create.  Status codes as above; lbm_batch_last_error gives
+ * All calls are made from one host thread.  Work goes to the stream given
+ * to lbm_batch_create and, where variants run side by side, to two streams of
+ * the batch's own: they start after what was enqueued before, and the given
+ * stream goes on after they have ended.  Status codes as above; lbm_batch_last_error gives
  * the message of the last failure.
  * ---------------------------------------------------------------------- */
 typedef struct lbm_batch lbm_batch;

@@ -1949,11 +1949,12 @@ lbm_block_kernel(const BlockArgs<P> ba) {
 // per two steps.  A step reaches two sites in every direction: 56 of the 64
 // columns are stored, and the first step walks two more rows at each end.
 //
-// What bounds it: vector issue (about 1450 instructions per row of two
-// steps; 77% of the issue slots of 2.4 GHz are used on 2048^2 float32), where
-// a step per launch is bound by memory (1.0 GB per step).  Two float32
-// wavefronts share a SIMD (190-202 registers, 18 KB of LDS each), one float64
-// wavefront has it alone.  Two columns per lane need 430 registers for
+// What bounds it: vector issue for float32 (about 1450 instructions per row of
+// two steps; the vector units of 2048^2 are 71% busy by the counters), where a
+// step per launch is bound by memory (1.0 GB per step); for float64 latency
+// too (55% busy).  Two float32 wavefronts share a SIMD (185-200 registers,
+// 18 KB of LDS each), one float64 wavefront has it alone (420-450 registers,
+// 4 of them spilled, 36 KB).  Two columns per lane need 430 registers for
 // float32: 135 us per step on 2048^2 against 132.
 // Measured per step on MI355X, lbm_step_kernel -> this: float32 1024^2
 // 47.0 -> 37.0 us, 2048x1024 97.9 -> 69.1, 2048^2 196 -> 132, 4096^2
@@ -3196,7 +3197,7 @@ constexpr size_t kOneWrite = 1u << 20;
 constexpr size_t kManyWrites = 12u << 20;
 // Not in a batch, whose simulations step meanwhile: with the joiners' initial
 // fields copied directly, the served burst of twelve float32 solves took 16 to
-// 20 ms (every other run 19 or more), through staging 15 to 16.6.
+// 20 ms (every other run 19 or more), through staging 15 to 16.
 
 // Making staging costs as much as it saves in several small transfers, so a
 // program's first two of up to kAtOnce, say the initial fields and the result

@@ -86,8 +86,10 @@ __device__ __forceinline__ float ninth_of<float>(float x) {
 // a b + c in one fused multiply-add.  The compiler fuses a sum of two
 // products, a b + c d, around one of them, and which one depends on the code
 // around it (the order in which the operands were loaded, what else uses a
-// product).  So such sums are spelled out: a site's bits are then the same
-// in every kernel that steps it.
+// product).  So such sums are spelled out, for a site to have the same bits in
+// every kernel that steps it.  Differences of two products are left to the
+// compiler, which fuses them alike in all of today's kernels: the tests compare
+// each variant of each kernel bit for bit.
 template <class R>
 __device__ __forceinline__ R fused(R a, R b, R c) {
   return __builtin_fma(a, b, c);
