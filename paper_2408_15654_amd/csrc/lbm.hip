@@ -2914,7 +2914,7 @@ struct lbm_handle {
   int block_plan;      // steps per launch of the block kernel (plan_block_steps)
   int block_steps;     // the plan in use: 0 under a tile height set by the caller
   bool of_batch;       // transfers of a batch's simulations always use staging
-  bool block_whole;    // launches of fewer steps than block_steps do not pay
+  bool block_short;    // its launches of one step pay (one_step_pays)
   std::string kernel;  // the step kernel variant, as a profiler names it
   std::string kernel_of_several;  // the kernel of several steps per launch, if planned
   std::string err;
@@ -3658,6 +3658,26 @@ hipError_t run_pair(lbm_handle *h, const BlockLaunch &l, int *waves_per_cu = nul
   return h->resident ? launch_pair<F32C>(h, l, waves_per_cu) : launch_pair<F32>(h, l, waves_per_cu);
 }
 
+// Whether a launch of the block kernel with one step is faster than
+// lbm_step_kernel's: where its blocks all run at once, and the walk that it
+// replaces is not among the shortest, which a block's fixed part outweighs:
+//  * float64: 32^2 to 222^2 7.3 -> 6.3 us to 8.1 -> 7.3, but with a prescribed
+//    velocity 4.8 -> 5.0 and 5.5 -> 6.0;
+//  * float32 and float16 with two columns per lane, or one where the tiles are
+//    of two rows: float32 60^2 6.8 -> 5.8, 260^2 (361 blocks) 7.7 -> 7.4, 300^2
+//    (484) 7.65 -> 7.7; float16 160^2 8.4 -> 7.1; prescribed float16 280^2
+//    (400) 7.2 -> 6.4, 290^2 (441) 7.1 -> 7.7; float32 280^2 6.0 -> 5.9, 310^2
+//    (529) 6.0 -> 6.7;
+//  * not with one column per lane and tiles of one row: float32 61x60 5.5 ->
+//    5.7, 201x200 6.0 -> 6.4; float16 161x160 6.7 -> 7.0; prescribed float32
+//    161x160 4.8 -> 5.1, float16 221x220 5.5 -> 6.0.
+bool one_step_pays(const lbm_handle *h, int cus, int resident) {
+  const int blocks = block_count(h->p, 1);
+  if (blocks > resident) return false;
+  if (h->p.precision == LBM_FP64) return h->ns;
+  return !(sites_per_lane(h->p) == 1 && h->rows == 1) && 3 * blocks <= 5 * cus;
+}
+
 // Time steps per launch of the block kernel, 0 where lbm_step_kernel is
 // faster.  A launch whose blocks all run at once costs its fixed part plus
 // its steps, and a second round of blocks doubles it, so the most steps are
@@ -3670,20 +3690,37 @@ hipError_t run_pair(lbm_handle *h, const BlockLaunch &l, int *waves_per_cu = nul
 //    6.33 with 1 and 7.9 for lbm_step_kernel; 176^2, 324 blocks, 6.67 against
 //    6.53 with 1.  float32 with the Navier-Stokes flow also gains with two
 //    rounds: 320x300, 960 blocks, 7.05 us against 7.68; 360x300, 1080
-//    blocks, 9.09 against 7.73.  There a launch of one step may take two
-//    rounds as well and then costs more than lbm_step_kernel's (320^2, 529
-//    blocks: 10.3 us against 7.8), which takes what whole launches leave
-//    (h->block_whole).
-//  * 1, if they are all resident: float64 210^2, 225 blocks, 7.01 us against
-//    8.17; float16 176^2, 195 blocks, 6.86 against 8.39; 210^2, 270 blocks,
-//    11.2 against 8.56.
+//    blocks, 9.09 against 7.73.
+//  * 1, if that pays (one_step_pays).
+// Calls of a few steps, and what is left of longer ones, take launches of one
+// step where they pay, else lbm_step_kernel (block_share).
 int plan_block_steps(lbm_handle *h, int cus, int resident) {
-  h->block_whole = block_count(h->p, 1) > resident;
   if (cus <= 0 || resident <= 0) return 0;
+  h->block_short = one_step_pays(h, cus, resident);
   if (block_count(h->p, kBlockMaxSteps) <= cus) return kBlockMaxSteps;
   const int rounds = h->p.precision == LBM_FP32 && h->ns ? 2 : 1;
   if (block_count(h->p, 2) <= rounds * resident) return 2;
-  return block_count(h->p, 1) <= resident ? 1 : 0;
+  return h->block_short ? 1 : 0;
+}
+
+// Steps of a call of n that launches of the block kernel take, and the number
+// of these: as few as can be with at most `most` steps each, at least two
+// where `one` step in a launch does not pay.  The call's launches are as many
+// as its steps but for an even number, since each goes from one copy of the
+// state to the other, and steps that a caller captures and replays have to end
+// on the copy that as many single steps end on.  `even`: the launches have to
+// be even in number.
+struct BlockShare {
+  int64_t steps, launches;
+};
+BlockShare block_share(int64_t n, int most, bool one, bool even) {
+  if (n < 2) return {0, 0};
+  for (int64_t steps = even ? n - n % 2 : n; steps > 0; steps -= even ? 2 : 1) {
+    int64_t launches = (steps + most - 1) / most;
+    launches += (steps - launches) % 2;
+    if (launches <= (one ? steps : steps / 2)) return {steps, launches};
+  }
+  return {0, 0};
 }
 
 // Default tile height of a single simulation.  A step costs about one
@@ -4061,15 +4098,9 @@ lbm_status lbm_step(lbm_handle *h, int64_t nsteps) {
     }
     return LBM_OK;
   };
-  // The launches are as many as the steps, but for an even number: each goes
-  // from one copy of the state to the other, and steps that a caller captures
-  // and replays have to end on the copy that as many single steps end on.
-  if (h->block_steps > 0 && left > 1) {
-    int64_t steps = flips ? left - left % 2 : left;  // the odd one goes in place
-    if (h->block_whole) steps -= steps % (2 * h->block_steps);
-    int64_t launches = (steps + h->block_steps - 1) / h->block_steps;
-    launches += (steps - launches) % 2;
-    const lbm_status st = alternate(launches, steps,
+  if (h->block_steps > 0) {
+    const BlockShare share = block_share(left, h->block_steps, h->block_short, flips);
+    const lbm_status st = alternate(share.launches, share.steps,
                                     [&](const BlockLaunch &l) { return run_block(h, l); });
     if (st != LBM_OK) return st;
   } else if (h->pair_tiles > 0) {
