@@ -3658,6 +3658,12 @@ hipError_t run_pair(lbm_handle *h, const BlockLaunch &l, int *waves_per_cu = nul
   return h->resident ? launch_pair<F32C>(h, l, waves_per_cu) : launch_pair<F32>(h, l, waves_per_cu);
 }
 
+// lbm_step_kernel's shortest walk: tiles of one row, one column per lane in
+// float32 arithmetic (5.5 us; with two columns 6.8, in float64 7.3).
+bool short_walk(const lbm_handle *h) {
+  return h->p.precision != LBM_FP64 && sites_per_lane(h->p) == 1 && h->rows == 1;
+}
+
 // Whether a launch of the block kernel with one step is faster than
 // lbm_step_kernel's: where its blocks all run at once, and the walk that it
 // replaces is not among the shortest, which a block's fixed part outweighs:
@@ -3675,7 +3681,7 @@ bool one_step_pays(const lbm_handle *h, int cus, int resident) {
   const int blocks = block_count(h->p, 1);
   if (blocks > resident) return false;
   if (h->p.precision == LBM_FP64) return h->ns;
-  return !(sites_per_lane(h->p) == 1 && h->rows == 1) && 3 * blocks <= 5 * cus;
+  return !short_walk(h) && 3 * blocks <= 5 * cus;
 }
 
 // Time steps per launch of the block kernel, 0 where lbm_step_kernel is
@@ -3688,9 +3694,12 @@ bool one_step_pays(const lbm_handle *h, int cus, int resident) {
 //    5.46 against 3.84 for float64, of which a compute unit holds one block.
 //  * 2, if they are all resident: float64 160^2, 256 blocks, 3.98 us against
 //    6.33 with 1 and 7.9 for lbm_step_kernel; 176^2, 324 blocks, 6.67 against
-//    6.53 with 1.  float32 with the Navier-Stokes flow also gains with two
-//    rounds: 320x300, 960 blocks, 7.05 us against 7.68; 360x300, 1080
-//    blocks, 9.09 against 7.73.
+//    6.53 with 1.  float32 with the Navier-Stokes flow also gains where two
+//    rounds take them, but not over tiles of one row with one column per lane.
+//    With equal densities 256^2, 676 blocks, 7.2 us -> 6.2, 316^2, 1024 blocks,
+//    7.4 -> 7.05, 231x230, 552 blocks, 5.85 -> 6.1; with different ones, whose
+//    blocks take longer, 256^2 7.5 -> 6.7, 280^2, 784 blocks, 7.7 -> 7.5, 281x280,
+//    812, 7.6 -> 7.7, 320x300, 960, 7.5 -> 7.85.
 //  * 1, if that pays (one_step_pays).
 // Calls of a few steps, and what is left of longer ones, take launches of one
 // step where they pay, else lbm_step_kernel (block_share).
@@ -3698,8 +3707,10 @@ int plan_block_steps(lbm_handle *h, int cus, int resident) {
   if (cus <= 0 || resident <= 0) return 0;
   h->block_short = one_step_pays(h, cus, resident);
   if (block_count(h->p, kBlockMaxSteps) <= cus) return kBlockMaxSteps;
-  const int rounds = h->p.precision == LBM_FP32 && h->ns ? 2 : 1;
-  if (block_count(h->p, 2) <= rounds * resident) return 2;
+  const int sixteenths = h->p.precision != LBM_FP32 || !h->ns || short_walk(h) ? 16
+                         : h->has_s                                            ? 25
+                                                                               : 32;
+  if (block_count(h->p, 2) <= resident * sixteenths / 16) return 2;
   return h->block_short ? 1 : 0;
 }
 

@@ -238,6 +238,7 @@ static void one_step_launches() {
                         {95, 94, LBM_FP16DEV, 1, true}, {290, 290, LBM_FP16DEV, 1, false}}) {
     lbm_params p = params(g.nx, g.ny, g.precision);
     p.flow = g.flow;
+    if (g.nx >= 300) p.rhoA = p.rhoB;
     Sim s(p);
     CHECK(s.init() == LBM_OK);
     for (int n = 1; n <= 19; ++n) {
@@ -252,6 +253,28 @@ static void one_step_launches() {
         std::exit(1);
       }
     }
+  }
+}
+
+// Blocks of two steps in two rounds (float32, 512 slots): up to both rounds
+// full with equal densities, to 800 blocks with different ones, and not where
+// lbm_step_kernel has one column per lane and tiles of one row.
+static void two_rounds() {
+  struct Grid {
+    int nx, ny;
+    double ratio;
+    bool block;
+  };
+  for (const Grid &g : {Grid{256, 256, 10, true}, {280, 280, 10, true}, {290, 290, 10, false},
+                        {310, 310, 10, false}, {290, 290, 1, true}, {320, 320, 1, true},
+                        {231, 230, 1, false}, {231, 230, 10, false}, {221, 220, 10, true}}) {
+    lbm_params p = params(g.nx, g.ny, LBM_FP32);
+    p.rhoA = g.ratio;
+    Sim s(p, 0, false);
+    int32_t steps = 0;
+    const std::string name = lbm_step_plan(s.h, &steps);
+    CHECK((name.rfind("lbm_block_kernel<", 0) == 0) == g.block);
+    CHECK(steps == (g.block ? 2 : 1));
   }
 }
 
@@ -425,6 +448,7 @@ int main(int argc, char **argv) {
       {"no_more_streams", no_more_streams},
       {"launch_parity", launch_parity},
       {"one_step_launches", one_step_launches},
+      {"two_rounds", two_rounds},
       {"tile_plan", tile_plan},
       {"unaligned_fields", unaligned_fields},
       {"pinned_memory", pinned_memory},

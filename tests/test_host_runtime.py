@@ -27,7 +27,8 @@ def host_check(tmp_path_factory):
 
 
 @pytest.mark.parametrize("check", ["other_device", "other_device_batch", "failed_chunk",
-                                   "no_more_streams", "launch_parity", "one_step_launches", "tile_plan",
+                                   "no_more_streams", "launch_parity", "one_step_launches", "two_rounds",
+                                   "tile_plan",
                                    "unaligned_fields", "pinned_memory", "first_transfers",
                                    "staged_writes", "batch_transfers"])
 def test_host_code(host_check, check):
