@@ -3869,7 +3869,9 @@ int query_pair_tiles(lbm_handle *h) {
     (void)hipGetLastError();
     return 0;
   }
-  return pair_tiles_of(h->p.nx, h->p.ny, h->p.precision == LBM_FP32, cus * per_cu / kXcds);
+  const double least =
+      pair_least_rows(h->p.precision == LBM_FP32, h->p.nx % 2 != 0, h->genr, h->has_s);
+  return pair_tiles_of(h->p.nx, h->p.ny, cus * per_cu / kXcds, least);
 }
 
 template <class P>

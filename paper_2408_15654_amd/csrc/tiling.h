@@ -45,18 +45,32 @@ constexpr int kPairHalo = 4;                   // columns on each side
 constexpr int kPairCols = 64 - 2 * kPairHalo;  // columns stored
 inline int pair_strips(int nx) { return (nx + kPairCols - 1) / kPairCols; }
 
-// Tiles per XCD of the two-step kernel, 0 where lbm_step_kernel is used:
-// grids whose tiles would be so low that the four rows a tile walks beyond
-// its own outweigh the gain.  All wavefront slots take one tile (slots: per
-// XCD), or as many as keep the tiles at 40 rows or fewer.  us per step,
-// lbm_step_kernel -> this: float32 600^2 (3.2 rows) 20.6 -> 20.9, 640^2
-// (3.75) 23.7 -> 21.2, 720^2 (4.6) 26.3 -> 24.0; float64 450^2 (3.9)
-// 22.5 -> 23.4, 512^2 (5.0) 27.0 -> 26.1.  4096^2 float32 with tiles of 148,
-// 74, 37 rows: 523, 497, 485; 2048^2 with 37 and 18 rows: 134.0 and 134.2.
-inline int pair_tiles_of(int nx, int ny, bool f32, int slots) {
+// Mean tile height from which the two-step kernel is faster than
+// lbm_step_kernel: below it the four rows a tile walks beyond its own outweigh
+// the gain.  us per step, lbm_step_kernel -> this:
+//  * float32 600^2 (3.2 rows) 20.6 -> 20.9, 640^2 (3.75) 23.7 -> 21.2, 720^2
+//    (4.6) 26.3 -> 24.0.  With odd nx lbm_step_kernel, one column per lane, is
+//    faster itself, and the variants whose sites take most arithmetic gain less
+//    (GENR: r != 1, HAS_S: rho_A != rho_B).  HAS_S alone: 633x640
+//    (3.75) 20.3 -> 20.5, 661^2 (3.9) 20.7 -> 20.6, 671x690 (4.0) 22.7 -> 22.3;
+//    both: 641x660 (3.9) 21.0 -> 21.4, 685x720 (4.6) 23.5 -> 24.1, 783x740
+//    (5.06) 27.0 -> 26.6;
+//  * float64 450^2 (3.9) 22.5 -> 23.4, 512^2 (5.0) 27.0 -> 26.1; both: 512^2
+//    27.6 -> 28.4, 526^2 (5.14) 28.6 -> 28.7, 534^2 (5.21) 29.2 -> 28.8.
+inline double pair_least_rows(bool f32, bool odd_nx, bool genr, bool has_s) {
+  if (!f32) return genr && has_s ? 5.2 : 4.7;
+  if (!odd_nx || !has_s) return 3.7;
+  return genr ? 5.0 : 3.85;
+}
+
+// Tiles per XCD of the two-step kernel, 0 where its tiles would be lower than
+// `least` rows.  All wavefront slots take one tile (slots: per XCD), or as many
+// as keep the tiles at 40 rows or fewer: 4096^2 float32 with tiles of 148, 74,
+// 37 rows 523, 497, 485 us per step; 2048^2 with 37 and 18 rows 134.0 and 134.2.
+inline int pair_tiles_of(int nx, int ny, int slots, double least) {
   if (slots <= 0 || ny < 16) return 0;  // the rows a tile reaches past the grid wrap once
   const double rows = double(pair_strips(nx)) * ny / kXcds / slots;  // mean tile height
-  if (rows < (f32 ? 3.7 : 4.7)) return 0;
+  if (rows < least) return 0;
   const long long tiles = (long long)slots * (long long)std::ceil(rows / 40.0);
   return int(std::max<long long>(tiles, pair_strips(nx)));  // a chunk per strip at least
 }

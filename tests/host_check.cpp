@@ -278,6 +278,31 @@ static void two_rounds() {
   }
 }
 
+// The tile heights from which the two-step kernel is taken, by storage, parity
+// of nx and variant (8 wavefronts of float32 and 4 of float64 to each of 256
+// compute units, as on the device).
+static void two_step_tiles() {
+  struct Grid {
+    int nx, ny, precision;
+    double r, ratio;
+    bool pair;
+  };
+  for (const Grid &g : {Grid{640, 640, LBM_FP32, 2, 10, true}, {633, 640, LBM_FP32, 2, 1, true},
+                        {633, 640, LBM_FP32, 1, 10, false}, {671, 672, LBM_FP32, 1, 10, true},
+                        {671, 690, LBM_FP32, 2, 10, false}, {685, 720, LBM_FP32, 2, 10, false},
+                        {785, 761, LBM_FP32, 2, 10, true}, {512, 512, LBM_FP64, 2, 1, true},
+                        {512, 512, LBM_FP64, 1, 10, true}, {512, 512, LBM_FP64, 2, 10, false},
+                        {560, 560, LBM_FP64, 2, 10, true}, {450, 450, LBM_FP64, 1, 1, false}}) {
+    lbm_params p = params(g.nx, g.ny, g.precision);
+    p.r = g.r, p.rhoA = g.ratio;
+    Sim s(p, 0, false);
+    int32_t steps = 0;
+    const std::string name = lbm_step_plan(s.h, &steps);
+    CHECK((name.rfind("lbm_pair_kernel<", 0) == 0) == g.pair);
+    CHECK(steps == (g.pair ? 2 : 1));
+  }
+}
+
 // Initial fields anywhere in memory, on no multiple of 8 bytes too: valid ones
 // reach the device as they are, and a value that is not finite is refused
 // wherever it stands.
@@ -449,6 +474,7 @@ int main(int argc, char **argv) {
       {"launch_parity", launch_parity},
       {"one_step_launches", one_step_launches},
       {"two_rounds", two_rounds},
+      {"two_step_tiles", two_step_tiles},
       {"tile_plan", tile_plan},
       {"unaligned_fields", unaligned_fields},
       {"pinned_memory", pinned_memory},

@@ -90,7 +90,7 @@ int hipLaunchKernel(const void *f, Dim3, Dim3, void **, size_t, void *) {
 }
 int hipOccupancyMaxActiveBlocksPerMultiprocessor(int *n, const void *f, int, size_t) {
   const std::string &k = kernels()[f];
-  *n = k.find("pair_kernel") != std::string::npos ? 8 : 2;
+  *n = k.find("pair_kernel") == std::string::npos ? 2 : k.find("F64") != std::string::npos ? 4 : 8;
   return kOk;
 }
 int hipGetDevice(int *d) { return *d = device, kOk; }

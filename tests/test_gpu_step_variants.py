@@ -64,7 +64,7 @@ def test_block_kernel(nx, ny, walls, r, ratio, precision, eos):
 @pytest.mark.parametrize("eos", ["linear", "langmuir"])
 @pytest.mark.parametrize("r,ratio", VARIANTS)
 @pytest.mark.parametrize("precision,nx,ny,walls,storage", [
-    ("fp32", 673, 641, True, "F32C"), ("fp32", 1601, 1300, False, "F32"),
+    ("fp32", 785, 761, True, "F32C"), ("fp32", 1601, 1300, False, "F32"),
     ("fp64", 561, 515, True, "F64C"), ("fp64", 1101, 1000, False, "F64")])
 def test_pair_kernel(precision, nx, ny, walls, storage, r, ratio, eos):
     name = assert_equal_to_single_steps(params(nx, ny, walls, r, ratio, eos, precision),

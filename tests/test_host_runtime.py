@@ -27,7 +27,7 @@ def host_check(tmp_path_factory):
 
 
 @pytest.mark.parametrize("check", ["other_device", "other_device_batch", "failed_chunk",
-                                   "no_more_streams", "launch_parity", "one_step_launches", "two_rounds",
+                                   "no_more_streams", "launch_parity", "one_step_launches", "two_rounds", "two_step_tiles",
                                    "tile_plan",
                                    "unaligned_fields", "pinned_memory", "first_transfers",
                                    "staged_writes", "batch_transfers"])

@@ -8,7 +8,7 @@
 
 // 0 if the tiles of an nx x ny grid on `slots` wavefronts per XCD are right.
 static int check(int nx, int ny, bool f32, int slots) {
-  const int tiles = pair_tiles_of(nx, ny, f32, slots), strips = pair_strips(nx);
+  const int tiles = pair_tiles_of(nx, ny, slots, f32 ? 3.7 : 4.7), strips = pair_strips(nx);
   if (tiles == 0) return 0;
   if (tiles < strips) return 1;
   int rows_done = 0;
