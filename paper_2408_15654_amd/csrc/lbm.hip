@@ -3658,10 +3658,12 @@ hipError_t run_pair(lbm_handle *h, const BlockLaunch &l, int *waves_per_cu = nul
   return h->resident ? launch_pair<F32C>(h, l, waves_per_cu) : launch_pair<F32>(h, l, waves_per_cu);
 }
 
-// lbm_step_kernel's shortest walk: tiles of one row, one column per lane in
-// float32 arithmetic (5.5 us; with two columns 6.8, in float64 7.3).
+// lbm_step_kernel's shortest walks, with one column per lane in float32
+// arithmetic: tiles of one row (5.5 us; with two columns 6.8, in float64 7.3),
+// and float16 storage's of two (6.4 to 7.1).
 bool short_walk(const lbm_handle *h) {
-  return h->p.precision != LBM_FP64 && sites_per_lane(h->p) == 1 && h->rows == 1;
+  if (h->p.precision == LBM_FP64 || sites_per_lane(h->p) == 2) return false;
+  return h->rows == 1 || h->p.precision == LBM_FP16DEV;
 }
 
 // Whether a launch of the block kernel with one step is faster than
@@ -3674,9 +3676,9 @@ bool short_walk(const lbm_handle *h) {
 //    (484) 7.65 -> 7.7; float16 160^2 8.4 -> 7.1; prescribed float16 280^2
 //    (400) 7.2 -> 6.4, 290^2 (441) 7.1 -> 7.7; float32 280^2 6.0 -> 5.9, 310^2
 //    (529) 6.0 -> 6.7;
-//  * not with one column per lane and tiles of one row: float32 61x60 5.5 ->
-//    5.7, 201x200 6.0 -> 6.4; float16 161x160 6.7 -> 7.0; prescribed float32
-//    161x160 4.8 -> 5.1, float16 221x220 5.5 -> 6.0.
+//  * not over the shortest walks: float32 61x60 5.5 -> 5.7, 201x200 6.0 -> 6.4;
+//    float16 161x160 6.7 -> 7.0, 257x159 7.1 -> 7.2; prescribed float32 161x160
+//    4.8 -> 5.1, float16 221x220 5.5 -> 6.0, 283x220 6.4 -> 6.55.
 bool one_step_pays(const lbm_handle *h, int cus, int resident) {
   const int blocks = block_count(h->p, 1);
   if (blocks > resident) return false;

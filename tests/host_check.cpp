@@ -235,7 +235,8 @@ static void one_step_launches() {
                         {310, 310, LBM_FP32, 1, false}, {60, 60, LBM_FP64, 1, true},
                         {160, 160, LBM_FP64, 1, true}, {230, 230, LBM_FP64, 1, false},
                         {95, 94, LBM_FP16DEV, 0, true}, {290, 290, LBM_FP16DEV, 0, false},
-                        {95, 94, LBM_FP16DEV, 1, true}, {290, 290, LBM_FP16DEV, 1, false}}) {
+                        {95, 94, LBM_FP16DEV, 1, true}, {290, 290, LBM_FP16DEV, 1, false},
+                        {231, 230, LBM_FP16DEV, 0, false}, {271, 270, LBM_FP16DEV, 1, false}}) {
     lbm_params p = params(g.nx, g.ny, g.precision);
     p.flow = g.flow;
     if (g.nx >= 300) p.rhoA = p.rhoB;
