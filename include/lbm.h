@@ -300,7 +300,7 @@ const char *lbm_step_plan(const lbm_handle *h, int32_t *steps);
  * float16 storage with even nx; Navier-Stokes or prescribed flow; r == 1
  * or not; equal densities or not); a chunk of those launches is captured
  * once as a HIP graph and replayed.  Variants do not touch each other: a
- * chunk of four steps and more is a graph per variant, which run side by
+ * chunk of more than a few steps is a graph per variant, which run side by
  * side.  The
  * arithmetic of each simulation is exactly that of lbm_step on its own
  * (bitwise), whatever the batch holds and whatever the schedule.

@@ -4627,11 +4627,14 @@ hipError_t make_lanes(lbm_batch *b, int lanes) {
 // float32 solves (three variants of 21, 15 and 11 us per step) 18.7 -> 13.2
 // ms, 22 -> 18.5 ms when the batch is new; nine float16 ones 19.0 -> 12.1 ms;
 // 180 steps of 32 channels (two variants, 80 and 27 us) 19.1 -> 17.5 ms.
-// Lanes and more graphs cost 20-40 us per chunk.  A chunk of 2 steps takes 101
-// -> 121 us for three variants of one 32x32 field, 223 -> 140 us for three of
-// two 200x200; of 4 steps 197 -> 198 us and 441 -> 232 us: so 4 steps or more
-// use them, and shorter chunks stay one graph on the caller's stream.
-constexpr int kLaneSteps = 4;
+// Lanes and more graphs cost 20-40 us per chunk, and gain the steps of all but
+// the longest variant.  us per chunk, one graph -> lanes: of 2 steps, three
+// variants of one 32x32 field 101 -> 121, of two 200x200 223 -> 140; of 4, 197 ->
+// 198 and 441 -> 232, but two variants of one 32x16 field 92 -> 111 and of one
+// 512x256 119 -> 128; of 5, these 118 -> 118 and 151 -> 151; of 8, 166 -> 146 and
+// 220 -> 204.  So two variants use them from 6 steps, three and more from 4, and
+// shorter chunks stay one graph on the caller's stream.
+int lane_steps(int variants) { return variants == 2 ? 6 : 4; }
 
 lbm_status launch_chunk(lbm_batch *b, int K) {
   int order[kClasses], present = 0;
@@ -4646,7 +4649,7 @@ lbm_status launch_chunk(lbm_batch *b, int K) {
     if (e != hipSuccess) return bhip(b, e, "synchronising");
     clear_graphs(b);
   }
-  int lanes = K >= kLaneSteps ? std::min(present, lbm_batch::kLanes) : 1;
+  int lanes = K >= lane_steps(present) ? std::min(present, lbm_batch::kLanes) : 1;
   if (lanes > 1) {  // a caller's capture sees its own stream only
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(b->stream, &cap) != hipSuccess) {

@@ -151,6 +151,28 @@ static void failed_chunk() {
   }
 }
 
+// From how many steps a chunk's variants run side by side, a graph each: two
+// variants from six, three from four.
+static void side_by_side() {
+  Stream stream{0};
+  lbm_batch *b = nullptr;
+  const std::vector<char> mem = batch_memory(&b, &stream);
+  submit(b, params(40, 30, LBM_FP64), 1000);
+  auto graphs_of = [&](int steps) {
+    graph_launches = 0;
+    CHECK(lbm_batch_step(b, steps) == LBM_OK);
+    return graph_launches;
+  };
+  for (const int steps : {1, 4, 32}) CHECK(graphs_of(steps) == 1);
+  submit(b, params(40, 20, LBM_FP32), 1000);
+  for (const int steps : {1, 4, 5}) CHECK(graphs_of(steps) == 1);
+  for (const int steps : {6, 7, 32}) CHECK(graphs_of(steps) == 2);
+  submit(b, params(40, 10, LBM_FP16DEV), 1000);
+  for (const int steps : {1, 3}) CHECK(graphs_of(steps) == 1);
+  for (const int steps : {4, 5, 32}) CHECK(graphs_of(steps) == 3);
+  lbm_batch_destroy(b);
+}
+
 // Where no more streams are to be had, a batch steps on the caller's alone.
 static void no_more_streams() {
   for (const int failures : {1, 2}) {
@@ -471,6 +493,7 @@ int main(int argc, char **argv) {
       {"other_device", other_device},
       {"other_device_batch", other_device_batch},
       {"failed_chunk", failed_chunk},
+      {"side_by_side", side_by_side},
       {"no_more_streams", no_more_streams},
       {"launch_parity", launch_parity},
       {"one_step_launches", one_step_launches},

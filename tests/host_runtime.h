@@ -36,6 +36,7 @@ inline std::vector<std::string> launched;            // kernels, in order
 inline std::map<char *, size_t> pinned;              // live pinned memory
 inline size_t pinned_made = 0;                       // bytes ever allocated
 inline int streams = 0, events = 0, graphs = 0;      // live objects
+inline int graph_launches = 0;
 inline int fail_graph_launch = -1;  // that launch of a graph fails (counted down)
 inline int fail_stream_create = 0;  // so many creations fail
 struct Copy {
@@ -193,6 +194,7 @@ int hipGraphExecDestroy(void *x) {
 }
 int hipGraphLaunch(void *, void *) {
   Lock lock(mu);
+  ++graph_launches;
   return fail_graph_launch >= 0 && fail_graph_launch-- == 0 ? kUnknown : kOk;
 }
 }  // extern "C"

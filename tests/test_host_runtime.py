@@ -26,7 +26,7 @@ def host_check(tmp_path_factory):
     return str(exe)
 
 
-@pytest.mark.parametrize("check", ["other_device", "other_device_batch", "failed_chunk",
+@pytest.mark.parametrize("check", ["other_device", "other_device_batch", "failed_chunk", "side_by_side",
                                    "no_more_streams", "launch_parity", "one_step_launches", "two_rounds", "two_step_tiles",
                                    "tile_plan",
                                    "unaligned_fields", "pinned_memory", "first_transfers",
